@@ -8,7 +8,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libqsv.so")
-SOURCES = ["kernels.hip", "combine.hip", "capi.cpp", "circuit.cpp", "planner.cpp", "emulate.cpp", "batch.cpp",
+SOURCES = ["kernels.hip", "generic.hip", "combine.hip", "capi.cpp", "circuit.cpp", "planner.cpp", "lower.cpp", "emulate.cpp", "batch.cpp",
            "jit.cpp", "tune.cpp", "dense.cpp", "partition.cpp", "noalloc.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
@@ -17,13 +17,16 @@ DEVICE_FLAGS = ["-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
                 # keep the per-thread amplitude array in registers: sinking the
                 # common stores of switch cases would address it through phis
                 "-mllvm", "-simplifycfg-sink-common=false"]
+# The interpreter's branches are uniform; structurized, every case of its
+# switch would copy the whole amplitude array.
+FILE_FLAGS = {"generic.hip": ["-mllvm", "-structurizecfg-skip-uniform-regions"]}
 COMMON = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-Wall",
           "-Wno-unused-function", "-Wno-unknown-pragmas"]
 
 
 def _compile(src):
     obj = os.path.join(BUILD, src + ".o")
-    cmd = [HIPCC] + COMMON + DEVICE_FLAGS + ["-c", os.path.join(CSRC, src), "-o", obj]
+    cmd = [HIPCC] + COMMON + DEVICE_FLAGS + FILE_FLAGS.get(src, []) + ["-c", os.path.join(CSRC, src), "-o", obj]
     if src.endswith(".cpp"):
         cmd = [HIPCC, "-x", "c++"] + [f for f in COMMON if not f.startswith("--offload")] + [
             "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-c", os.path.join(CSRC, src), "-o", obj]

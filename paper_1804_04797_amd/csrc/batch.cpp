@@ -11,12 +11,12 @@
 //  - states of 2^21 amplitudes or more: compiled kernels of their own plan
 //    on the tile shape autotuned for their class (one launch per plan and
 //    pass, all entries of the plan in its grid).
-// The generic-kernel classes run as one launch per tile shape and pass
-// round, ordered by kernel boundaries.  A persistent form (one launch per
-// tile shape over work items (pass round, entry, tile) taken in order from a
-// device counter, per-entry counters of completed tiles ordering each
-// entry's passes, BatchRound) is built but switched off: its first runs on
-// the device did not finish and the cause is not yet found.  The launches
+// The generic-kernel classes run as one launch per tile shape and program
+// round (a pass is one program, a very long one several), ordered by kernel
+// boundaries.  The schedule of a persistent form (work items (pass round,
+// entry, tile) taken in order from a device counter, BatchRound) is kept for
+// its host check; its kernel did not finish on the device and is gone.  The
+// launches
 // and the closing gather of every entry's sampled amplitudes are captured
 // once into a hipGraph and replayed: one graph launch per run.
 #include <hip/hip_runtime.h>
@@ -40,19 +40,12 @@ struct BatchShape {
     std::vector<uint32_t> entries;
     std::vector<int> round_seg_off, round_nseg;  // per-round launches: their segments
     std::vector<uint64_t> round_blocks;
-    std::vector<qsv::BatchRound> rounds;         // persistent launch
-    uint64_t items = 0;
-    unsigned grid = 0;
-    qsv::BatchRound *d_rounds = nullptr;         // into the batch's table block
-    qsv::BatchSeg *d_segs = nullptr;
-    unsigned long long *d_next = nullptr;
+    qsv::BatchSeg *d_segs = nullptr;             // into the batch's table block
 };
 
 struct qsv_batch {
     int R = 0, T = 0, c = 0;
     bool forced_shape = false;  // opts gave a tile shape: every generic entry uses it
-    bool persistent = false;    // one persistent launch per tile shape (switched off, see sv_batch_create)
-    uint32_t wait_us = 200000;  // longest wait of one persistent work item
     int jit_mode = 0;  // opts->jit: 1 always, -1 never, 0 for plans shared by >= 8 entries
     std::vector<std::vector<uint32_t>> group;       // entries of each plan
     std::vector<char> plan_jit;                     // plan runs as compiled kernels
@@ -64,14 +57,9 @@ struct qsv_batch {
     std::vector<std::shared_ptr<qsv::Plan>> plans;
     std::vector<uint32_t> entry_plan;
     std::vector<BatchShape> shapes;
-    qsv::PassProg *d_progs = nullptr;
+    qsv::GenProg *d_progs = nullptr;
     qsv::BatchEntry *d_ents = nullptr;
-    void *d_tabs = nullptr;           // rounds, segments and counters of every shape
-    uint32_t *d_done = nullptr;       // per entry: completed tiles (persistent launches)
-    uint32_t *d_err = nullptr;        // a bounded wait gave up
-    size_t n_counters = 0;            // 32-bit words cleared before every run
-    uint32_t *h_abort = nullptr;      // pinned host flag polled by the waits
-    uint32_t *d_abort = nullptr;      // its device address
+    void *d_tabs = nullptr;           // segments of every shape
     std::vector<qsv::BatchEntry> h_ents;
     // captured graph and the arguments it was captured for
     hipGraphExec_t exec = nullptr;
@@ -105,8 +93,6 @@ void free_tables(qsv_batch *b) {
     b->d_progs = nullptr;
     b->d_ents = nullptr;
     b->d_tabs = nullptr;
-    b->d_done = nullptr;
-    b->d_err = nullptr;
     b->shapes.clear();
 }
 
@@ -125,6 +111,8 @@ constexpr int kBigState = 21;
 // none, 47.2 with 2, 45.6 with 4, 45.8 with 8, 46.1 with 16)
 constexpr int kLanes = 4;
 constexpr int kLdsState = 14;
+// entries that share a plan from which on its kernels are compiled
+constexpr size_t kSharedPlan = 8;
 bool big_state(const qsv_batch *b, int n) { return b->jit_mode >= 0 && n >= kBigState; }
 
 // Tile shape (R, T) with R + T = n for a state held by one tile.
@@ -172,6 +160,8 @@ qsv_status build_tables(qsv_batch *b, int lb) {
     b->plans.clear();
     b->entry_plan.assign(b->circs.size(), 0);
     std::map<const qsv_circuit *, uint32_t> idx;
+    std::map<const qsv_circuit *, size_t> sharers;
+    for (const qsv_circuit *c : b->circs) ++sharers[c];
     std::vector<TileShape> plan_shape;
     for (size_t i = 0; i < b->circs.size(); ++i) {
         auto it = idx.find(b->circs[i]);
@@ -194,6 +184,11 @@ qsv_status build_tables(qsv_batch *b, int lb) {
                 }
             } else if (!b->forced_shape && c->n <= kLdsState && lds_shape(c->n, &lr, &lt)) {
                 sh = TileShape{lr, lt, std::min(5, lt + 1)};
+            } else if (!b->forced_shape && b->jit_mode >= 0 && (b->jit_mode > 0 || sharers[c] >= kSharedPlan)) {
+                // compiled passes over many states fill the device anyway, and
+                // the larger tile has fewer exchanges (2 x 1024 branch states
+                // of 15 qubits: 315 us against 387 us on (4, 8, 4))
+                sh = TileShape{5, 8, 5};
             }
             PlanKey key{lb, -1, sh.R, sh.T, sh.c, false};
             std::shared_ptr<Plan> p;
@@ -220,7 +215,7 @@ qsv_status build_tables(qsv_batch *b, int lb) {
     b->plan_jit.assign(b->plans.size(), 0);
     b->d_group_ents.assign(b->plans.size(), nullptr);
     for (size_t p = 0; p < b->plans.size(); ++p) {
-        const bool shared = b->group[p].size() >= 8;
+        const bool shared = b->group[p].size() >= kSharedPlan;
         const bool big = big_state(b, b->plans[p]->n);
         b->plan_jit[p] = !b->plans[p]->passes.empty() &&
                          (b->jit_mode > 0 || (b->jit_mode == 0 && (shared || big))) &&
@@ -231,12 +226,17 @@ qsv_status build_tables(qsv_batch *b, int lb) {
             if (e != hipSuccess) return fail(QSV_ENOMEM, "sv_batch: group entry table");
         }
     }
-    // program array
-    std::vector<PassProg> progs;
-    std::vector<uint32_t> prog0(b->plans.size());
+    // program array of the generic kernel's plans
+    std::vector<GenProg> progs;
+    std::vector<uint32_t> prog0(b->plans.size(), 0), prog_count(b->plans.size(), 0);
     for (size_t p = 0; p < b->plans.size(); ++p) {
+        if (b->plan_jit[p]) continue;
+        std::shared_ptr<const std::vector<GenProg>> g;
+        const qsv_status st = generic_programs(*b->plans[p], false, g);
+        if (st != QSV_OK) return st;
         prog0[p] = uint32_t(progs.size());
-        for (const Pass &ps : b->plans[p]->passes) progs.push_back(ps.prog);
+        prog_count[p] = uint32_t(g->size());
+        progs.insert(progs.end(), g->begin(), g->end());
     }
     // entries
     b->h_ents.assign(b->circs.size(), BatchEntry{});
@@ -248,8 +248,7 @@ qsv_status build_tables(qsv_batch *b, int lb) {
         e.n = uint32_t(b->circs[i]->n);
         e.init_val = float(std::pow(2.0, -0.5 * e.n));
     }
-    // generic-kernel entries by tile shape: segments of every pass round
-    // (block / item offsets within the round) and the persistent schedule
+    // generic-kernel entries by tile shape: segments of every program round
     std::map<std::pair<int, int>, size_t> shape_of;
     for (size_t i = 0; i < b->circs.size(); ++i) {
         const uint32_t p = b->entry_plan[i];
@@ -273,66 +272,44 @@ qsv_status build_tables(qsv_batch *b, int lb) {
         std::vector<size_t> np;
         for (uint32_t i : bs.entries) {
             nq.push_back(b->circs[i]->n);
-            np.push_back(b->plans[b->entry_plan[i]]->passes.size());
+            np.push_back(prog_count[b->entry_plan[i]]);
         }
-        make_schedule(nq, np, bs.entries, bs.R + bs.T, bs.rounds, shape_segs[k], bs.round_blocks, bs.items);
-        for (const BatchRound &rd : bs.rounds) {
+        std::vector<BatchRound> rounds;
+        uint64_t items = 0;
+        make_schedule(nq, np, bs.entries, bs.R + bs.T, rounds, shape_segs[k], bs.round_blocks, items);
+        for (const BatchRound &rd : rounds) {
             bs.round_seg_off.push_back(int(rd.seg_off));
             bs.round_nseg.push_back(int(rd.nseg));
         }
         for (uint64_t blocks : bs.round_blocks)
             if (blocks > (1ull << 31)) return fail(QSV_ERANGE, "sv_batch: too many tiles in one round");
-        const uint64_t items = bs.items;
-        unsigned resident = 0;
-        hipError_t e = launch_fused_persistent(bs.R, bs.T, nullptr, 0, nullptr, 0, nullptr, nullptr, 0, nullptr,
-                                               nullptr, nullptr, nullptr, 0, 0, nullptr, &resident);
-        if (e != hipSuccess) return hipfail(e, "sv_batch: occupancy of the persistent kernel");
-        bs.grid = unsigned(std::min<uint64_t>(items, resident));
     }
     hipError_t e;
     if (!progs.empty()) {
-        e = hipMalloc(reinterpret_cast<void **>(&b->d_progs), progs.size() * sizeof(PassProg));
+        e = hipMalloc(reinterpret_cast<void **>(&b->d_progs), progs.size() * sizeof(GenProg));
         if (e != hipSuccess) return fail(QSV_ENOMEM, "sv_batch: program table");
-        e = hipMemcpy(b->d_progs, progs.data(), progs.size() * sizeof(PassProg), hipMemcpyHostToDevice);
+        e = hipMemcpy(b->d_progs, progs.data(), progs.size() * sizeof(GenProg), hipMemcpyHostToDevice);
         if (e != hipSuccess) return hipfail(e, "sv_batch: program upload");
     }
     e = hipMalloc(reinterpret_cast<void **>(&b->d_ents), b->h_ents.size() * sizeof(BatchEntry));
     if (e != hipSuccess) return fail(QSV_ENOMEM, "sv_batch: entry table");
-    // one block for the schedule tables and the counters: per shape its
-    // rounds and segments, then (cleared before every run) the per-entry
-    // done counters, the error word and each shape's item counter
+    // one block for the segments of every shape
     size_t bytes = 0;
-    std::vector<size_t> off_r(b->shapes.size()), off_s(b->shapes.size()), off_n(b->shapes.size());
-    auto align = [](size_t x) { return (x + 255) & ~size_t(255); };
+    std::vector<size_t> off_s(b->shapes.size());
     for (size_t k = 0; k < b->shapes.size(); ++k) {
-        off_r[k] = bytes;
-        bytes = align(bytes + b->shapes[k].rounds.size() * sizeof(BatchRound));
         off_s[k] = bytes;
-        bytes = align(bytes + shape_segs[k].size() * sizeof(BatchSeg));
+        bytes += (shape_segs[k].size() * sizeof(BatchSeg) + 255) & ~size_t(255);
     }
-    const size_t off_c = bytes;
-    const size_t off_err = off_c + b->circs.size() * sizeof(uint32_t);
-    size_t off_next = align(off_err + sizeof(uint32_t));
-    for (size_t k = 0; k < b->shapes.size(); ++k) off_n[k] = off_next + k * sizeof(unsigned long long);
-    bytes = off_next + b->shapes.size() * sizeof(unsigned long long);
-    b->n_counters = (bytes - off_c) / sizeof(uint32_t);
-    e = hipMalloc(&b->d_tabs, bytes);
-    if (e != hipSuccess) return fail(QSV_ENOMEM, "sv_batch: schedule tables");
-    char *base = static_cast<char *>(b->d_tabs);
-    std::vector<char> h(off_c, 0);
-    for (size_t k = 0; k < b->shapes.size(); ++k) {
-        BatchShape &bs = b->shapes[k];
-        if (!bs.rounds.empty()) std::memcpy(h.data() + off_r[k], bs.rounds.data(), bs.rounds.size() * sizeof(BatchRound));
-        if (!shape_segs[k].empty())
-            std::memcpy(h.data() + off_s[k], shape_segs[k].data(), shape_segs[k].size() * sizeof(BatchSeg));
-        bs.d_rounds = reinterpret_cast<BatchRound *>(base + off_r[k]);
-        bs.d_segs = reinterpret_cast<BatchSeg *>(base + off_s[k]);
-        bs.d_next = reinterpret_cast<unsigned long long *>(base + off_n[k]);
-    }
-    b->d_done = reinterpret_cast<uint32_t *>(base + off_c);
-    b->d_err = reinterpret_cast<uint32_t *>(base + off_err);
-    if (off_c) {
-        e = hipMemcpy(b->d_tabs, h.data(), off_c, hipMemcpyHostToDevice);
+    if (bytes) {
+        e = hipMalloc(&b->d_tabs, bytes);
+        if (e != hipSuccess) return fail(QSV_ENOMEM, "sv_batch: schedule tables");
+        std::vector<char> h(bytes, 0);
+        for (size_t k = 0; k < b->shapes.size(); ++k) {
+            if (!shape_segs[k].empty())
+                std::memcpy(h.data() + off_s[k], shape_segs[k].data(), shape_segs[k].size() * sizeof(BatchSeg));
+            b->shapes[k].d_segs = reinterpret_cast<BatchSeg *>(static_cast<char *>(b->d_tabs) + off_s[k]);
+        }
+        e = hipMemcpy(b->d_tabs, h.data(), bytes, hipMemcpyHostToDevice);
         if (e != hipSuccess) return hipfail(e, "sv_batch: schedule upload");
     }
     b->built_lb = lb;
@@ -364,7 +341,7 @@ qsv_status sv_batch_create(const qsv_circuit *const *circs, const uint64_t *bran
     // generic-kernel tile shape of the states that one tile cannot hold
     // (the LDS class has a shape per qubit count); opts may force one shape
     // for every generic entry
-    b->R = 5;
+    b->R = 4;  // see default_shape
     b->T = 8;
     if (opts && opts->reg_qubits && opts->thread_qubits) {
         b->R = opts->reg_qubits;
@@ -374,15 +351,13 @@ qsv_status sv_batch_create(const qsv_circuit *const *circs, const uint64_t *bran
         if (!ok) return fail(QSV_EUNSUPPORTED, "sv_batch_create: no batch kernel for this tile shape");
         if (b->R + b->T > nmin) return fail(QSV_EUNSUPPORTED, "sv_batch_create: tile larger than a state");
     }
-    b->c = (opts && opts->low_qubits) ? opts->low_qubits : std::min(5, b->T + 1);
+    b->c = (opts && opts->low_qubits) ? opts->low_qubits : b->forced_shape ? std::min(5, b->T + 1) : 4;
     b->jit_mode = opts ? opts->jit : 0;
-    // The persistent launch is switched off: its first runs on the device did
-    // not finish (the cause is not yet found), so asking for it is refused
-    // and every batch runs one launch per pass round.
+    // There is no persistent launch (its kernel did not finish on the device):
+    // asking for it is refused and every batch runs one launch per round.
     if (const char *v = std::getenv("QSV_BATCH_PERSISTENT"))
         if (v[0] != '0')
             return fail(QSV_EUNSUPPORTED, "sv_batch_create: the persistent batch launch is switched off");
-    if (const char *v = std::getenv("QSV_BATCH_WAIT_US")) b->wait_us = uint32_t(std::strtoul(v, nullptr, 10));
     b->circs.assign(circs, circs + count);
     b->branches.assign(count, 0);
     if (branch_ids) b->branches.assign(branch_ids, branch_ids + count);
@@ -390,13 +365,8 @@ qsv_status sv_batch_create(const qsv_circuit *const *circs, const uint64_t *bran
     hipError_t e = hipSuccess;
     static const int kShapes[][2] = {{5, 9}, {5, 8}, {4, 8}, {5, 7}, {4, 7}};
     for (auto &sh : kShapes)
-        if (e == hipSuccess) e = launch_fused_batch(sh[0], sh[1], nullptr, 0, nullptr, nullptr, 0, 0, 0, nullptr);
+        if (e == hipSuccess) e = launch_tile_batch(sh[0], sh[1], nullptr, 0, nullptr, nullptr, 0, 0, 0, nullptr);
     if (e != hipSuccess) return fail(QSV_EHIP, std::string("sv_batch_create: ") + hipGetErrorString(e));
-    e = hipHostMalloc(reinterpret_cast<void **>(&b->h_abort), sizeof(uint32_t), hipHostMallocCoherent);
-    if (e != hipSuccess) return fail(QSV_ENOMEM, "sv_batch_create: abort flag");
-    *b->h_abort = 0;
-    e = hipHostGetDevicePointer(reinterpret_cast<void **>(&b->d_abort), b->h_abort, 0);
-    if (e != hipSuccess) return fail(QSV_EHIP, "sv_batch_create: abort flag device address");
     e = hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking);
     if (e != hipSuccess) return fail(QSV_EHIP, "sv_batch_create: capture stream");
     *out = b.release();
@@ -481,8 +451,7 @@ qsv_status sv_batch_run(qsv_batch *b, void *const *amps_dev, int init_plus,
         }
         e = hipStreamBeginCapture(b->cap, hipStreamCaptureModeThreadLocal);
         if (e != hipSuccess) return hipfail(e, "sv_batch_run: begin capture");
-        // counters of the persistent launches start at zero in every replay
-        hipError_t le = b->persistent ? launch_zero_u32(b->d_done, b->n_counters, b->cap) : hipSuccess;
+        hipError_t le = hipSuccess;
         // Each compiled plan's passes form a chain of their own: the chains
         // go to the side streams (largest work first, each to the least
         // loaded stream), so the graph holds them as parallel branches and
@@ -514,16 +483,9 @@ qsv_status sv_batch_run(qsv_batch *b, void *const *amps_dev, int init_plus,
         }
         for (const BatchShape &bs : b->shapes) {
             if (le != hipSuccess) break;
-            if (b->persistent) {
-                le = launch_fused_persistent(bs.R, bs.T, bs.d_rounds, int(bs.rounds.size()), bs.d_segs, bs.items,
-                                             b->d_ents, b->d_progs, init_plus ? 1 : 0, b->d_done, bs.d_next,
-                                             b->d_err, b->d_abort, b->wait_us, bs.grid, b->cap, nullptr);
-            } else {
-                for (size_t r = 0; r < bs.round_blocks.size() && le == hipSuccess; ++r)
-                    le = launch_fused_batch(bs.R, bs.T, bs.d_segs + bs.round_seg_off[r], bs.round_nseg[r],
-                                            b->d_ents, b->d_progs, int(r), bs.round_blocks[r],
-                                            init_plus ? 1 : 0, b->cap);
-            }
+            for (size_t r = 0; r < bs.round_blocks.size() && le == hipSuccess; ++r)
+                le = launch_tile_batch(bs.R, bs.T, bs.d_segs + bs.round_seg_off[r], bs.round_nseg[r], b->d_ents,
+                                       b->d_progs, int(r), bs.round_blocks[r], init_plus ? 1 : 0, b->cap);
         }
         // join every side stream back (also after an error: the capture
         // must end with all of them joined)
@@ -558,20 +520,13 @@ qsv_status sv_batch_run(qsv_batch *b, void *const *amps_dev, int init_plus,
 
 qsv_status sv_batch_status(qsv_batch *b, void *stream) {
     if (!b) return fail(QSV_EINVAL, "sv_batch_status: null batch");
-    if (!b->d_err) return QSV_OK;  // never run
-    uint32_t err = 0;
-    hipError_t e = hipStreamSynchronize(static_cast<hipStream_t>(stream));
-    if (e == hipSuccess) e = hipMemcpy(&err, b->d_err, sizeof(err), hipMemcpyDeviceToHost);
-    if (e != hipSuccess) return hipfail(e, "sv_batch_status");
-    __atomic_store_n(b->h_abort, 0u, __ATOMIC_SEQ_CST);  // the queued work is done: later runs wait again
-    if (err) return fail(QSV_EINTERNAL, "sv_batch_status: a bounded wait of the persistent launch gave up");
-    return QSV_OK;
+    const hipError_t e = hipStreamSynchronize(static_cast<hipStream_t>(stream));
+    return e == hipSuccess ? QSV_OK : hipfail(e, "sv_batch_status");
 }
 
 qsv_status sv_batch_abort(qsv_batch *b) {
-    if (!b || !b->h_abort) return fail(QSV_EINVAL, "sv_batch_abort: null batch");
-    __atomic_store_n(b->h_abort, 1u, __ATOMIC_SEQ_CST);
-    return QSV_OK;
+    if (!b) return fail(QSV_EINVAL, "sv_batch_abort: null batch");
+    return QSV_OK;  // no launch of a batch waits on another one
 }
 
 // Host emulation of a persistent launch's schedule (CPU check of the
@@ -658,7 +613,6 @@ void sv_batch_destroy(qsv_batch *b) {
     for (hipStream_t ls : b->lanes) hipStreamDestroy(ls);
     for (hipEvent_t ev : b->lane_done) hipEventDestroy(ev);
     if (b->fork) hipEventDestroy(b->fork);
-    if (b->h_abort) hipHostFree(b->h_abort);
     delete b;
 }
 

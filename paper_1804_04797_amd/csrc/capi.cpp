@@ -155,9 +155,8 @@ const qsv_fuse_opts *effective_opts(const qsv_circuit *c, const qsv_fuse_opts *o
 }
 
 qsv_status resolve_shape(const qsv_circuit *c, const qsv_fuse_opts *opts, TileShape &sh,
-                         int lb = 0, int le = -1) {
-    (void)lb; (void)le;
-    sh = default_shape(c->n);
+                         bool gate_order = false) {
+    sh = default_shape(c->n, gate_order);
     if (opts) {
         if (opts->reg_qubits) sh.R = opts->reg_qubits;
         if (opts->thread_qubits) sh.T = opts->thread_qubits;
@@ -282,13 +281,30 @@ void gate_matrix_f32(uint8_t kind, float m[8]) {
 
 }  // namespace
 
+// Every lowered program of the plan (at least one) on amps; the first one
+// reads src, or starts from the initial state of kind init (>= 0).
+static qsv_status run_generic(Plan &plan, bool gate_order, const void *src, void *amps, uint64_t branch, int init,
+                              uint64_t basis, hipStream_t s, const char *who) {
+    std::shared_ptr<const std::vector<GenProg>> progs;
+    qsv_status st = generic_programs(plan, gate_order, progs);
+    if (st != QSV_OK) return st;
+    const float2 *in = static_cast<const float2 *>(src);
+    for (const GenProg &p : *progs) {
+        hipError_t e = launch_tile(in, static_cast<float2 *>(amps), plan.n, plan.R, plan.T, p, branch, init, basis, s);
+        if (e != hipSuccess) return fail(QSV_EHIP, std::string(who) + ": " + hipGetErrorString(e));
+        in = static_cast<const float2 *>(amps);
+        init = -1;
+    }
+    return QSV_OK;
+}
+
 // Per-pass times of the sweep as sv_simulate runs it from |+>^n (the
 // autotuner's choice of kernel form per pass).
 qsv_status time_sweep_passes(const qsv_circuit *c, int lb, int le, const qsv_fuse_opts *opts,
                              void *amps, void *workspace, size_t ws_bytes, hipStream_t s,
                              uint64_t max_tiles, std::vector<float> &ms) {
     TileShape sh;
-    qsv_status st = resolve_shape(c, opts, sh, lb, le);
+    qsv_status st = resolve_shape(c, opts, sh, true);
     if (st != QSV_OK) return st;
     const int jm = jit_mode(c, opts);
     if (sh.R == 0 || !jm) return fail(QSV_EUNSUPPORTED, "pass timing needs compiled pass kernels");
@@ -452,7 +468,7 @@ qsv_status sv_apply_fused(void *amps, const qsv_circuit *c, uint64_t branch, int
     opts = effective_opts(c, opts, layer_begin, layer_end, &tuned);
     if (opts && opts->plain) return sv_apply_plain(amps, c, branch, layer_begin, layer_end, stream);
     TileShape sh;
-    if ((st = resolve_shape(c, opts, sh, layer_begin, layer_end)) != QSV_OK) return st;
+    if ((st = resolve_shape(c, opts, sh)) != QSV_OK) return st;
     if (sh.R == 0) return sv_apply_plain(amps, c, branch, layer_begin, layer_end, stream);
     if ((st = check_device()) != QSV_OK) return st;
     std::shared_ptr<Plan> plan;
@@ -474,11 +490,7 @@ qsv_status sv_apply_fused(void *amps, const qsv_circuit *c, uint64_t branch, int
     if (!fused_shape_supported(sh.R, sh.T))
         return fail(QSV_EUNSUPPORTED, "sv_apply_fused: this tile shape runs compiled passes only (jit >= 1)");
     if ((st = get_plan(c, layer_begin, layer_end, sh, plan)) != QSV_OK) return st;
-    for (const Pass &p : plan->passes) {
-        hipError_t e = launch_fused(static_cast<float2 *>(amps), c->n, sh.R, sh.T, p.prog, branch, s);
-        if (e != hipSuccess) return hip_fail(e, "sv_apply_fused");
-    }
-    return QSV_OK;
+    return run_generic(*plan, false, amps, amps, branch, -1, 0, s, "sv_apply_fused");
 }
 
 qsv_status sv_apply_fused_from(const void *src, void *dst, const qsv_circuit *c, uint64_t branch,
@@ -501,7 +513,7 @@ qsv_status sv_apply_fused_from(const void *src, void *dst, const qsv_circuit *c,
     TileShape sh;
     bool fused = !(opts && opts->plain);
     if (fused) {
-        if ((st = resolve_shape(c, opts, sh, layer_begin, layer_end)) != QSV_OK) return st;
+        if ((st = resolve_shape(c, opts, sh)) != QSV_OK) return st;
         fused = sh.R != 0;
     }
     const int jm = fused ? jit_mode(c, opts) : 0;
@@ -525,7 +537,12 @@ qsv_status sv_apply_fused_from(const void *src, void *dst, const qsv_circuit *c,
         }
         return jit_launch(*plan, variant, dst, scratch, branch, 0, nullptr, s, nullptr, src);
     }
-    // generic kernel or per-gate path: copy, then sweep dst in place
+    if (fused && fused_shape_supported(sh.R, sh.T)) {  // generic kernel: its first program reads src
+        std::shared_ptr<Plan> plan;
+        if ((st = get_plan(c, layer_begin, layer_end, sh, plan)) != QSV_OK) return st;
+        if (!plan->passes.empty()) return run_generic(*plan, false, src, dst, branch, -1, 0, s, "sv_apply_fused_from");
+    }
+    // per-gate path or no gates: copy, then sweep dst in place
     hipError_t e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToDevice, s);
     if (e != hipSuccess) return hip_fail(e, "sv_apply_fused_from: copy");
     return sv_apply_fused(dst, c, branch, layer_begin, layer_end, opts, workspace, ws_bytes, stream);
@@ -571,7 +588,7 @@ static qsv_status sampler_create(const qsv_circuit *c, int layer_begin, int laye
     const qsv_fuse_opts *eo = effective_opts(c, opts, layer_begin, layer_end, &tuned);
     bool fused = !(eo && eo->plain);
     if (fused) {
-        if ((st = resolve_shape(c, eo, S->sh, layer_begin, layer_end)) != QSV_OK) return st;
+        if ((st = resolve_shape(c, eo, S->sh)) != QSV_OK) return st;
         fused = S->sh.R != 0;
     }
     S->jm = fused ? jit_mode(c, eo) : 0;
@@ -1003,7 +1020,7 @@ qsv_status sv_simulate(void *amps, const qsv_circuit *c, uint64_t branch, int in
     TileShape sh;
     bool fused = !(opts && opts->plain);
     if (fused) {
-        if ((st = resolve_shape(c, opts, sh, layer_begin, layer_end)) != QSV_OK) return st;
+        if ((st = resolve_shape(c, opts, sh, true)) != QSV_OK) return st;
         fused = sh.R != 0;
     }
     std::shared_ptr<Plan> plan;
@@ -1039,11 +1056,18 @@ qsv_status sv_simulate(void *amps, const qsv_circuit *c, uint64_t branch, int in
         const size_t need = norm_out_dev ? norm_partial_count(c->n) * sizeof(double) : 0;
         if (need && (!ws.p || ws.bytes < need))
             return fail(QSV_EINVAL, "sv_simulate: the FP64 norm needs a workspace of sv_workspace_bytes bytes");
-        hipError_t e = launch_init(static_cast<float2 *>(amps), c->n, init_kind, basis, s);
-        if (e != hipSuccess) return hip_fail(e, "sv_simulate");
-        st = fused ? sv_apply_fused(amps, c, branch, layer_begin, layer_end, opts, workspace, ws_bytes, stream)
-                   : sv_apply_plain(amps, c, branch, layer_begin, layer_end, stream);
-        if (st != QSV_OK) return st;
+        hipError_t e = hipSuccess;
+        if (fused && !plan->passes.empty()) {
+            // the first program generates the initial state
+            if (!fused_shape_supported(sh.R, sh.T))
+                return fail(QSV_EUNSUPPORTED, "sv_simulate: this tile shape runs compiled passes only (jit >= 1)");
+            if ((st = run_generic(*plan, true, amps, amps, branch, init_kind, basis, s, "sv_simulate")) != QSV_OK)
+                return st;
+        } else {
+            e = launch_init(static_cast<float2 *>(amps), c->n, init_kind, basis, s);
+            if (e != hipSuccess) return hip_fail(e, "sv_simulate");
+            if (!fused && (st = sv_apply_plain(amps, c, branch, layer_begin, layer_end, stream)) != QSV_OK) return st;
+        }
         if (norm_out_dev) {
             e = launch_norm(static_cast<const float2 *>(amps), c->n, norm_out_dev, reinterpret_cast<double *>(ws.p),
                             s);
@@ -1080,7 +1104,7 @@ qsv_status sv_simulate_dot(void *amps, const qsv_circuit *c, uint64_t branch, in
     TileShape sh;
     bool fused = !(opts && opts->plain);
     if (fused) {
-        if ((st = resolve_shape(c, opts, sh, layer_begin, layer_end)) != QSV_OK) return st;
+        if ((st = resolve_shape(c, opts, sh, true)) != QSV_OK) return st;
         fused = sh.R != 0;
     }
     const int jm = fused ? jit_mode(c, opts) : 0;
@@ -1169,7 +1193,7 @@ qsv_status sv_workspace_bytes(const qsv_circuit *c, int layer_begin, int layer_e
     TileShape sh{0, 0, 0};
     const bool fused = !(opts && opts->plain);
     if (fused) {
-        qsv_status st = resolve_shape(c, opts, sh, layer_begin, layer_end);
+        qsv_status st = resolve_shape(c, opts, sh);
         if (st != QSV_OK) return st;
     }
     const int jm = (fused && sh.R) ? jit_mode(c, opts) : 0;
@@ -1186,7 +1210,7 @@ qsv_status sv_plan_info(const qsv_circuit *c, int layer_begin, int layer_end,
     qsv_fuse_opts tuned;
     opts = effective_opts(c, opts, layer_begin, layer_end, &tuned);
     TileShape sh;
-    qsv_status st = resolve_shape(c, opts, sh, layer_begin, layer_end);
+    qsv_status st = resolve_shape(c, opts, sh);
     if (st != QSV_OK) return st;
     if (sh.R == 0) return fail(QSV_EUNSUPPORTED, "sv_plan_info: state too small for a tile");
     std::shared_ptr<Plan> plan;
@@ -1229,8 +1253,23 @@ qsv_status sv_debug_emulate(void *amps_host, const qsv_circuit *c, uint64_t bran
     if ((st = select_plan(c, layer_begin, layer_end, sh, oop_mode(c, opts, jit_mode(c, opts)), true,
                           plan)) != QSV_OK)
         return st;
-    // the same buffer schedule as the device sweep
     float *amps = static_cast<float *>(amps_host);
+    if (!jit_mode(c, opts) && fused_shape_supported(sh.R, sh.T)) {  // the generic kernel's programs
+        std::shared_ptr<const std::vector<GenProg>> progs;
+        // sv_simulate's programs on a copy: both forms are checked
+        std::vector<float> ordered(amps, amps + (size_t(2) << c->n));
+        float most = 0.f;  // largest component of the start: no gate makes a state longer
+        for (float x : ordered) most = std::max(most, std::fabs(x));
+        if ((st = generic_programs(*plan, true, progs)) != QSV_OK) return st;
+        for (const GenProg &p : *progs) emulate_gen(p, c->n, sh.R, sh.T, branch, ordered.data());
+        if ((st = generic_programs(*plan, false, progs)) != QSV_OK) return st;
+        for (const GenProg &p : *progs) emulate_gen(p, c->n, sh.R, sh.T, branch, amps);
+        for (size_t i = 0; i < ordered.size(); ++i)
+            if (!(std::fabs(ordered[i] - amps[i]) <= 1e-5f * most)) 
+                return fail(QSV_EINTERNAL, "sv_debug_emulate: the lowered forms differ");
+        return QSV_OK;
+    }
+    // the same buffer schedule as the device sweep
     std::vector<float> second(plan->oop ? size_t(2) << c->n : 0);
     const size_t np = plan->passes.size();
     const float *in = amps;

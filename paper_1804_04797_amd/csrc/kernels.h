@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include "genprog.h"
 #include "qsv_internal.h"
 
 namespace qsv {
@@ -13,20 +14,15 @@ bool fused_shape_supported(int R, int T);
 // amplitudes, whose exchanges only fit LDS staged in halves (one tile per
 // workgroup; compiled passes only)
 bool compiled_shape_supported(int R, int T);
-hipError_t launch_fused(float2 *amps, int n, int R, int T, const PassProg &p, uint64_t branch,
-                        hipStream_t s);
-hipError_t launch_fused_batch(int R, int T, const BatchSeg *segs, int nseg, const BatchEntry *ents,
-                              const PassProg *progs, int round, uint64_t blocks, int init_plus,
-                              hipStream_t s);
-// One persistent launch over every work item of a tile shape's rounds (see
-// BatchRound).  resident != NULL: only report the workgroups the device holds
-// at once (no launch).  abort: pinned host flag the waits poll; wait_us:
-// longest wait of one work item before it gives up.
-hipError_t launch_fused_persistent(int R, int T, const BatchRound *rounds, int nrounds, const BatchSeg *segs,
-                                   uint64_t total, const BatchEntry *ents, const PassProg *progs, int init_plus,
-                                   uint32_t *done, unsigned long long *next, uint32_t *err, const uint32_t *abort,
-                                   uint32_t wait_us, unsigned grid, hipStream_t s, unsigned *resident);
-hipError_t launch_zero_u32(uint32_t *p, uint64_t count, hipStream_t s);
+// One lowered program over every tile of a state (generic.hip): reads src (amps,
+// or another state, which stays as it is) and writes amps.  init >= 0: the
+// tiles start from the initial state of that kind (sv_init) instead.
+hipError_t launch_tile(const float2 *src, float2 *amps, int n, int R, int T, const GenProg &p, uint64_t branch,
+                       int init, uint64_t basis, hipStream_t s);
+// One program round of a batch: `blocks` tiles of the entries in segs.
+// blocks == 0 only prepares the kernel (outside a capture).
+hipError_t launch_tile_batch(int R, int T, const BatchSeg *segs, int nseg, const BatchEntry *ents,
+                             const GenProg *progs, int round, uint64_t blocks, int init_plus, hipStream_t s);
 hipError_t launch_gather_batch(const BatchEntry *ents, uint64_t count, const uint64_t *xs,
                                uint64_t m, float2 *out, hipStream_t s);
 hipError_t launch_dense(float2 *amps, int n, int k, const int *qubits, const float *mat_t,

@@ -20,395 +20,8 @@ __device__ __forceinline__ float2 f2(float x, float y) { return make_float2(x, y
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef float v2f __attribute__((ext_vector_type(2)));
 
-// e^{i pi k / 4}, k = 0..7
-__constant__ float c_wr[8] = {1.f, 0.70710678118654752f, 0.f, -0.70710678118654752f,
-                              -1.f, -0.70710678118654752f, 0.f, 0.70710678118654752f};
-__constant__ float c_wi[8] = {0.f, 0.70710678118654752f, 1.f, 0.70710678118654752f,
-                              0.f, -0.70710678118654752f, -1.f, -0.70710678118654752f};
-
-// ---------------------------------------------------------------------------
-// Register-slot primitives.  v[j] holds the amplitude whose register-slot
-// bits are j; slot S pairs v[j] with v[j | 2^S].
-// ---------------------------------------------------------------------------
-
-template <int S, int N> __device__ __forceinline__ void bf_h(float2 (&v)[N]) {
-#pragma unroll
-    for (int j = 0; j < N; ++j) {
-        if (j & (1 << S)) continue;
-        const float2 x = v[j], y = v[j | (1 << S)];
-        v[j] = f2(x.x + y.x, x.y + y.y);
-        v[j | (1 << S)] = f2(x.x - y.x, x.y - y.y);
-    }
-}
-template <int S, int N> __device__ __forceinline__ void bf_sx(float2 (&v)[N]) {
-#pragma unroll
-    for (int j = 0; j < N; ++j) {
-        if (j & (1 << S)) continue;
-        const float2 x = v[j], y = v[j | (1 << S)];
-        v[j] = f2(x.x + y.y, x.y - y.x);            // x - i y
-        v[j | (1 << S)] = f2(y.x + x.y, y.y - x.x); // y - i x
-    }
-}
-template <int S, int N> __device__ __forceinline__ void bf_sy(float2 (&v)[N]) {
-#pragma unroll
-    for (int j = 0; j < N; ++j) {
-        if (j & (1 << S)) continue;
-        const float2 x = v[j], y = v[j | (1 << S)];
-        v[j] = f2(x.x - y.x, x.y - y.y);
-        v[j | (1 << S)] = f2(x.x + y.x, x.y + y.y);
-    }
-}
-template <int S, int N> __device__ __forceinline__ void bf_sxdg(float2 (&v)[N]) {
-#pragma unroll
-    for (int j = 0; j < N; ++j) {
-        if (j & (1 << S)) continue;
-        const float2 x = v[j], y = v[j | (1 << S)];
-        v[j] = f2(x.x - y.y, x.y + y.x);            // x + i y
-        v[j | (1 << S)] = f2(y.x - x.y, y.y + x.x); // y + i x
-    }
-}
-template <int S, int N> __device__ __forceinline__ void bf_sydg(float2 (&v)[N]) {
-#pragma unroll
-    for (int j = 0; j < N; ++j) {
-        if (j & (1 << S)) continue;
-        const float2 x = v[j], y = v[j | (1 << S)];
-        v[j] = f2(x.x + y.x, x.y + y.y);
-        v[j | (1 << S)] = f2(y.x - x.x, y.y - x.y);
-    }
-}
 __device__ __forceinline__ float2 cmul(float2 a, float cr, float ci) {
     return f2(a.x * cr - a.y * ci, a.x * ci + a.y * cr);
-}
-// multiply amplitudes with slot bit S = 1 by (cr, ci)
-template <int S, int N> __device__ __forceinline__ void ph_slot(float2 (&v)[N], float cr, float ci) {
-#pragma unroll
-    for (int j = 0; j < N; ++j)
-        if (j & (1 << S)) v[j] = cmul(v[j], cr, ci);
-}
-template <int S, int N> __device__ __forceinline__ void neg_slot(float2 (&v)[N]) {
-#pragma unroll
-    for (int j = 0; j < N; ++j)
-        if (j & (1 << S)) v[j] = f2(-v[j].x, -v[j].y);
-}
-template <int S1, int S2, int N> __device__ __forceinline__ void neg_slot2(float2 (&v)[N]) {
-#pragma unroll
-    for (int j = 0; j < N; ++j)
-        if ((j & (1 << S1)) && (j & (1 << S2))) v[j] = f2(-v[j].x, -v[j].y);
-}
-// zero amplitudes whose slot bit S differs from l
-template <int S, int N> __device__ __forceinline__ void proj_slot(float2 (&v)[N], int l) {
-    if (l) {
-#pragma unroll
-        for (int j = 0; j < N; ++j)
-            if (!(j & (1 << S))) v[j] = f2(0.f, 0.f);
-    } else {
-#pragma unroll
-        for (int j = 0; j < N; ++j)
-            if (j & (1 << S)) v[j] = f2(0.f, 0.f);
-    }
-}
-
-// Dispatch a runtime register-slot index to a compile-time template.  The
-// last slot is the default so that every path of the switch computes: an
-// empty path would make the register allocator copy the whole amplitude
-// array at the merge.
-#define QSV_SLOT_DISPATCH(s, CALL)                                                  \
-    switch (s) {                                                                    \
-    case 0: if constexpr (R - 1 > 0) { constexpr int S_ = 0; CALL; break; } [[fallthrough]]; \
-    case 1: if constexpr (R - 1 > 1) { constexpr int S_ = 1; CALL; break; } [[fallthrough]]; \
-    case 2: if constexpr (R - 1 > 2) { constexpr int S_ = 2; CALL; break; } [[fallthrough]]; \
-    case 3: if constexpr (R - 1 > 3) { constexpr int S_ = 3; CALL; break; } [[fallthrough]]; \
-    case 4: if constexpr (R - 1 > 4) { constexpr int S_ = 4; CALL; break; } [[fallthrough]]; \
-    default: { constexpr int S_ = R - 1; CALL; } break;                             \
-    }
-
-// negate amplitudes with slot bit S = 1 when m has the sign bit set
-template <int S, int N> __device__ __forceinline__ void xneg_slot(float2 (&v)[N], uint32_t m) {
-#pragma unroll
-    for (int j = 0; j < N; ++j)
-        if (j & (1 << S))
-            v[j] = f2(__uint_as_float(__float_as_uint(v[j].x) ^ m),
-                      __uint_as_float(__float_as_uint(v[j].y) ^ m));
-}
-// zero amplitudes whose slot bit S differs from l (branch-free)
-template <int S, int N> __device__ __forceinline__ void proj_sel(float2 (&v)[N], uint32_t l) {
-#pragma unroll
-    for (int j = 0; j < N; ++j) {
-        const bool z = (uint32_t((j >> S) & 1) != l);
-        v[j] = z ? f2(0.f, 0.f) : v[j];
-    }
-}
-template <int R, int S1, int N>
-__device__ __forceinline__ void cz_reg_reg(float2 (&v)[N], uint32_t s2) {
-    // the slot pair is distinct by construction; S1 == S2 cannot occur
-    QSV_SLOT_DISPATCH(s2, (neg_slot2<S1, S_, N>(v)));
-}
-
-// ---------------------------------------------------------------------------
-// Fused tile pass (generic: interprets a pass program).
-//
-// One workgroup of 2^T threads owns one tile of 2^(R+T) amplitudes: slot
-// coordinate x = j | t << R (j = register index, t = thread index) sits at
-// physical index base | sum_{s: x_s = 1} 2^{phys[s]}.  Loads and stores are
-// 16-byte (two amplitudes: register slot 0 is physical bit 0) and the thread
-// slots 0..c-2 hold physical bits 1..c-1, so each wave access is made of
-// contiguous runs of 2^c amplitudes.  XCHG permutes slot bits through LDS
-// (write at padded old coordinate, read at padded new coordinate; one pad
-// element per 2^R keeps the 64 lanes of a wave on distinct banks).
-// Diagonal gates whose qubit is a thread or tile-index bit multiply every
-// amplitude of a thread by the same power of w = e^{i pi/4}: they only add to
-// the per-thread exponent e, applied before an XCHG (when the op says so) and
-// by the closing SCALE.
-// init: 0 = load the tile, 1 = every amplitude = init_val (|+>^n).
-// ---------------------------------------------------------------------------
-template <int R, int T>
-__device__ __forceinline__ void fused_tile(float2 *__restrict__ amps, const PassProg &P,
-                                           uint64_t branch, uint64_t tile, int init,
-                                           float init_val, float2 *lds) {
-    constexpr int N = 1 << R;
-    const uint32_t t = threadIdx.x;
-
-    uint64_t base = 0;  // tile origin in the map the pass reads
-    for (int i = 0; i < P.n_glob; ++i) base |= ((tile >> i) & 1ull) << P.glob_bits[i];
-
-    float2 v[N];
-    if (init) {
-#pragma unroll
-        for (int j = 0; j < N; ++j) v[j] = f2(init_val, 0.f);
-    } else {
-        uint64_t toff = 0;
-#pragma unroll
-        for (int u = 0; u < T; ++u)
-            if ((t >> u) & 1u) toff |= 1ull << P.ld_phys[R + u];
-        const float2 *src = amps + (base | toff);
-#pragma unroll
-        for (int j = 0; j < N; j += 2) {
-            uint64_t roff = 0;
-#pragma unroll
-            for (int s = 1; s < R; ++s)
-                if ((j >> s) & 1) roff |= 1ull << P.ld_phys[s];
-            const v4f w = __builtin_nontemporal_load(reinterpret_cast<const v4f *>(src + roff));
-            v[j] = f2(w.x, w.y);
-            v[j + 1] = f2(w.z, w.w);
-        }
-    }
-
-    auto pred = [&](uint32_t loc) -> uint32_t {
-        if (loc & 0x80u) return uint32_t((base >> (loc & 0x7fu)) & 1ull);
-        return (t >> (loc - R)) & 1u;
-    };
-    uint32_t e = 0, alive = 1;
-
-    int pc = 0;
-    do {
-        const uint64_t op = P.ops[pc];
-        const uint32_t code = uint32_t(op) & 0xffu;
-        const uint32_t a = uint32_t(op >> 8) & 0xffu;
-        const uint32_t b = uint32_t(op >> 16) & 0xffu;
-        const uint32_t c = uint32_t(op >> 24) & 0xffu;
-        switch (code) {
-        case 1: QSV_SLOT_DISPATCH(a, (bf_h<S_, N>(v))); break;
-        case 2: QSV_SLOT_DISPATCH(a, (bf_sx<S_, N>(v))); break;
-        case 3: QSV_SLOT_DISPATCH(a, (bf_sy<S_, N>(v))); break;
-        case 4: QSV_SLOT_DISPATCH(a, (bf_sxdg<S_, N>(v))); break;
-        case 5: QSV_SLOT_DISPATCH(a, (bf_sydg<S_, N>(v))); break;
-        case 8: {  // PHASE
-            if (a < uint32_t(R)) {
-                const float cr = c_wr[b], ci = c_wi[b];
-                QSV_SLOT_DISPATCH(a, (ph_slot<S_, N>(v, cr, ci)));
-            } else {
-                e += pred(a) * b;
-            }
-            break;
-        }
-        case 9: {  // CZ
-            uint32_t x = a, y = b;
-            if (x >= uint32_t(R) && y < uint32_t(R)) { uint32_t tmp = x; x = y; y = tmp; }
-            if (x < uint32_t(R) && y < uint32_t(R)) {
-                QSV_SLOT_DISPATCH(x, (cz_reg_reg<R, S_, N>(v, y)));
-            } else if (x < uint32_t(R)) {
-                const uint32_t m = pred(y) << 31;
-                QSV_SLOT_DISPATCH(x, (xneg_slot<S_, N>(v, m)));
-            } else {
-                e += (pred(x) & pred(y)) * 4u;
-            }
-            break;
-        }
-        case 10: {  // PROJ
-            const uint32_t l = c ? uint32_t((branch >> b) & 1ull) : b;
-            if (a < uint32_t(R)) {
-                QSV_SLOT_DISPATCH(a, (proj_sel<S_, N>(v, l)));
-            } else {
-                alive &= uint32_t(pred(a) == l);
-            }
-            break;
-        }
-        case 11: {  // ZB
-            const uint32_t bit = uint32_t((branch >> b) & 1ull);
-            if (a < uint32_t(R)) {
-                QSV_SLOT_DISPATCH(a, (xneg_slot<S_, N>(v, bit << 31)));
-            } else {
-                e += (bit & pred(a)) * 4u;
-            }
-            break;
-        }
-        case 12: {  // XCHG: new slot s takes old slot perm[s]
-            const uint64_t pw = P.ops[++pc];
-            {   // phases accumulated on thread/tile bits are applied first
-                // (unconditionally: a skipped path would cost a full copy of v)
-                const float fr = alive ? c_wr[e & 7u] : 0.f, fi = alive ? c_wi[e & 7u] : 0.f;
-#pragma unroll
-                for (int j = 0; j < N; ++j) v[j] = cmul(v[j], fr, fi);
-                e = 0;
-                alive = 1;
-                (void)c;
-            }
-            __syncthreads();  // earlier reads of LDS are complete
-            const uint32_t wt = (t << R) + t;  // padded old coordinate of (t, 0)
-#pragma unroll
-            for (int j = 0; j < N; ++j) lds[wt + j] = v[j];
-            uint32_t yt = 0;
-#pragma unroll
-            for (int u = 0; u < T; ++u)
-                if ((t >> u) & 1u) yt |= 1u << ((pw >> (4 * (R + u))) & 0xf);
-            const uint32_t rt = yt + (yt >> R);
-            __syncthreads();
-#pragma unroll
-            for (int j = 0; j < N; ++j) {
-                uint32_t yj = 0;
-#pragma unroll
-                for (int s = 0; s < R; ++s)
-                    if ((j >> s) & 1) yj |= 1u << ((pw >> (4 * s)) & 0xf);
-                v[j] = lds[rt + yj + (yj >> R)];
-            }
-            break;
-        }
-        default: {  // SCALE (closes every program): pass scale x w^e x alive
-            const float wr = alive ? c_wr[e & 7u] : 0.f, wi = alive ? c_wi[e & 7u] : 0.f;
-            const float cr = P.scale_re * wr - P.scale_im * wi;
-            const float ci = P.scale_re * wi + P.scale_im * wr;
-#pragma unroll
-            for (int j = 0; j < N; ++j) v[j] = cmul(v[j], cr, ci);
-            e = 0;
-            alive = 1;
-            break;
-        }
-        }
-    } while (++pc < P.n_ops);
-
-    {
-        uint64_t bst = 0;  // tile origin in the map the pass writes
-        for (int i = 0; i < P.n_glob; ++i) bst |= ((tile >> i) & 1ull) << P.glob_st[i];
-        uint64_t toff = 0;
-#pragma unroll
-        for (int u = 0; u < T; ++u)
-            if ((t >> u) & 1u) toff |= 1ull << P.st_phys[R + u];
-        float2 *dst = amps + (bst | toff);
-#pragma unroll
-        for (int j = 0; j < N; j += 2) {
-            uint64_t roff = 0;
-#pragma unroll
-            for (int s = 1; s < R; ++s)
-                if ((j >> s) & 1) roff |= 1ull << P.st_phys[s];
-            const v4f w = {v[j].x, v[j].y, v[j + 1].x, v[j + 1].y};
-            __builtin_nontemporal_store(w, reinterpret_cast<v4f *>(dst + roff));
-        }
-    }
-}
-
-template <int R, int T>
-__global__ void __launch_bounds__(1 << T)
-k_fused(float2 *__restrict__ amps, const PassProg P, uint64_t branch, uint64_t tile0) {
-    extern __shared__ float2 lds[];
-    fused_tile<R, T>(amps, P, branch, tile0 + blockIdx.x, 0, 0.f, lds);
-}
-
-// One pass round of a batch: block b belongs to the segment with the largest
-// start <= b; the segment names the entry (state, branch, program) and the
-// first tile.  Entries whose round is their first pass may generate |+>^n.
-template <int R, int T>
-__global__ void __launch_bounds__(1 << T)
-k_fused_batch(const BatchSeg *__restrict__ segs, int nseg, const BatchEntry *__restrict__ ents,
-              const PassProg *__restrict__ progs, int round, int init_plus) {
-    extern __shared__ float2 lds[];
-    const uint64_t blk = blockIdx.x;
-    int lo = 0, hi = nseg - 1;
-    while (lo < hi) {  // last segment with start <= blk
-        const int mid = (lo + hi + 1) >> 1;
-        if (segs[mid].start <= blk) lo = mid; else hi = mid - 1;
-    }
-    const BatchSeg sg = segs[lo];
-    const BatchEntry en = ents[sg.entry];
-    const PassProg &P = progs[en.prog0 + round];
-    const int init = (init_plus && round == 0) ? 1 : 0;
-    fused_tile<R, T>(reinterpret_cast<float2 *>(en.amps), P, en.branch, blk - sg.start, init,
-                     en.init_val, lds);
-}
-
-// Persistent form of a batch's generic tile passes: one launch for every
-// pass round of every entry of one tile shape.  Workgroups take work items
-// (round, entry, tile) in order from *next (batch_decode); an item of round
-// r > 0 first waits until done[entry] reaches r * tiles(entry), i.e. until
-// every tile of the entry's earlier passes is stored.  The device has one L2
-// per XCD, so the counters are updated and polled with system-scope atomics
-// (performed past the XCD caches), a tile's stores are written back
-// (system-scope release fence of every wave) before its entry's counter is
-// raised, and the waiting workgroup invalidates its caches (acquire fence)
-// once the counter has reached its target, before any wave loads.  Every
-// wait is bounded in time: after wait_ticks ticks of the constant-rate
-// device clock, or when the host sets *abort (pinned host memory, polled
-// every 256 tries), the workgroup records the failure in *err and goes on,
-// so the launch always drains within a bounded time.
-template <int R, int T>
-__global__ void __launch_bounds__(1 << T)
-k_fused_persistent(const BatchRound *__restrict__ rounds, int nrounds, const BatchSeg *__restrict__ segs,
-                   uint64_t total, const BatchEntry *__restrict__ ents, const PassProg *__restrict__ progs,
-                   int init_plus, uint32_t *done, unsigned long long *next, uint32_t *err,
-                   const volatile uint32_t *abort, uint64_t wait_ticks) {
-    extern __shared__ float2 lds[];
-    __shared__ unsigned long long item_s;
-    constexpr int L = R + T;
-    for (;;) {
-        if (threadIdx.x == 0)
-            item_s = __hip_atomic_fetch_add(next, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-        __syncthreads();
-        const uint64_t item = item_s;
-        __syncthreads();  // every wave has the item before it is overwritten
-        if (item >= total) break;
-        int r = 0;
-        uint32_t e = 0;
-        uint64_t tile = 0;
-        batch_decode(rounds, nrounds, segs, item, &r, &e, &tile);
-        const BatchEntry en = ents[e];
-        if (r > 0) {
-            if (threadIdx.x == 0) {
-                const uint32_t need = uint32_t(r) << (en.n - L);
-                const uint64_t t0 = wall_clock64();
-                for (uint32_t k = 1;
-                     __hip_atomic_load(done + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) < need; ++k) {
-                    if (wall_clock64() - t0 > wait_ticks || ((k & 255u) == 0 && *abort)) {
-                        __hip_atomic_fetch_or(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-                        break;
-                    }
-                    __builtin_amdgcn_s_sleep(2);
-                }
-            }
-            __syncthreads();
-            __atomic_thread_fence(__ATOMIC_ACQUIRE);  // system scope: drop stale cached lines
-        }
-        fused_tile<R, T>(reinterpret_cast<float2 *>(en.amps), progs[en.prog0 + r], en.branch, tile,
-                         (init_plus && r == 0) ? 1 : 0, en.init_val, lds);
-        __threadfence_system();  // this wave's stores are written back
-        __syncthreads();         // ... for every wave of the tile
-        if (threadIdx.x == 0) __hip_atomic_fetch_add(done + e, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    }
-}
-
-// Clears the counters of a persistent batch launch (a kernel, not a memset:
-// it is replayed inside the batch's graph).
-__global__ void __launch_bounds__(256) k_zero_u32(uint32_t *__restrict__ p, uint64_t count) {
-    const uint64_t stride = uint64_t(gridDim.x) * blockDim.x;
-    for (uint64_t i = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; i < count; i += stride) p[i] = 0u;
 }
 
 // Gather for every entry of a batch: out[e*m + k] = amps_e[xs[e*m + k]].
@@ -1047,124 +660,7 @@ unsigned grid_for(uint64_t work, unsigned per_block = 256, unsigned cap = 1u << 
     return unsigned(g);
 }
 
-template <int R, int T>
-hipError_t launch_fused_t(float2 *amps, int n, const PassProg &p, uint64_t branch, hipStream_t s) {
-    constexpr int L = R + T;
-    const size_t lds = (size_t(1) << L) * sizeof(float2) + (size_t(1) << T) * sizeof(float2);
-    static bool attr_set = false;
-    if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_fused<R, T>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
-        if (e != hipSuccess) return e;
-        attr_set = true;
-    }
-    const uint64_t tiles = 1ull << (n - L);
-    const uint64_t chunk = 1ull << 30;  // blocks per launch
-    for (uint64_t t0 = 0; t0 < tiles; t0 += chunk) {
-        const uint64_t cnt = (tiles - t0 < chunk) ? tiles - t0 : chunk;
-        hipLaunchKernelGGL((k_fused<R, T>), dim3(unsigned(cnt)), dim3(1 << T), lds, s, amps, p,
-                           branch, t0);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
-}
-
-template <int R, int T>
-hipError_t launch_fused_batch_t(const BatchSeg *segs, int nseg, const BatchEntry *ents,
-                                const PassProg *progs, int round, uint64_t blocks, int init_plus,
-                                hipStream_t s) {
-    constexpr int L = R + T;
-    const size_t lds = (size_t(1) << L) * sizeof(float2) + (size_t(1) << T) * sizeof(float2);
-    static bool attr_set = false;
-    if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_fused_batch<R, T>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
-        if (e != hipSuccess) return e;
-        attr_set = true;
-    }
-    if (blocks == 0) return hipSuccess;
-    if (blocks > (1ull << 31)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_fused_batch<R, T>), dim3(unsigned(blocks)), dim3(1 << T), lds, s, segs,
-                       nseg, ents, progs, round, init_plus);
-    return hipGetLastError();
-}
-
-template <int R, int T>
-hipError_t launch_fused_persistent_t(const BatchRound *rounds, int nrounds, const BatchSeg *segs, uint64_t total,
-                                     const BatchEntry *ents, const PassProg *progs, int init_plus, uint32_t *done,
-                                     unsigned long long *next, uint32_t *err, const uint32_t *abort,
-                                     uint32_t wait_us, unsigned grid, hipStream_t s, unsigned *resident) {
-    constexpr int L = R + T;
-    const size_t lds = (size_t(1) << L) * sizeof(float2) + (size_t(1) << T) * sizeof(float2);
-    static bool attr_set = false;
-    if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_fused_persistent<R, T>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
-        if (e != hipSuccess) return e;
-        attr_set = true;
-    }
-    if (resident) {  // workgroups the device holds at once
-        int per_cu = 0, dev = 0, cus = 0;
-        hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &per_cu, reinterpret_cast<const void *>(&k_fused_persistent<R, T>), 1 << T, lds);
-        if (e == hipSuccess) e = hipGetDevice(&dev);
-        if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-        if (e != hipSuccess) return e;
-        *resident = unsigned(std::max(1, per_cu) * std::max(1, cus));
-        return hipSuccess;
-    }
-    if (total == 0 || grid == 0) return hipSuccess;
-    int dev = 0, khz = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e == hipSuccess) e = hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev);
-    if (e != hipSuccess) return e;
-    const uint64_t wait_ticks = uint64_t(wait_us) * uint64_t(khz > 0 ? khz : 100000) / 1000u;
-    hipLaunchKernelGGL((k_fused_persistent<R, T>), dim3(grid), dim3(1 << T), lds, s, rounds, nrounds, segs, total,
-                       ents, progs, init_plus, done, next, err, reinterpret_cast<const volatile uint32_t *>(abort),
-                       wait_ticks);
-    return hipGetLastError();
-}
-
 }  // namespace
-
-hipError_t launch_fused_persistent(int R, int T, const BatchRound *rounds, int nrounds, const BatchSeg *segs,
-                                   uint64_t total, const BatchEntry *ents, const PassProg *progs, int init_plus,
-                                   uint32_t *done, unsigned long long *next, uint32_t *err, const uint32_t *abort,
-                                   uint32_t wait_us, unsigned grid, hipStream_t s, unsigned *resident) {
-#define QSV_PERSIST(RR, TT)                                                                                     \
-    case RR * 16 + TT:                                                                                          \
-        return launch_fused_persistent_t<RR, TT>(rounds, nrounds, segs, total, ents, progs, init_plus, done, next, \
-                                                 err, abort, wait_us, grid, s, resident);
-    switch (R * 16 + T) {
-        QSV_PERSIST(5, 9)
-        QSV_PERSIST(5, 8)
-        QSV_PERSIST(4, 8)
-        QSV_PERSIST(5, 7)
-        QSV_PERSIST(4, 7)
-    default: return hipErrorInvalidValue;
-    }
-#undef QSV_PERSIST
-}
-
-hipError_t launch_zero_u32(uint32_t *p, uint64_t count, hipStream_t s) {
-    if (count == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_zero_u32, dim3(grid_for(count, 256, 1024)), dim3(256), 0, s, p, count);
-    return hipGetLastError();
-}
-
-hipError_t launch_fused_batch(int R, int T, const BatchSeg *segs, int nseg, const BatchEntry *ents,
-                              const PassProg *progs, int round, uint64_t blocks, int init_plus,
-                              hipStream_t s) {
-    switch (R * 16 + T) {
-    case 5 * 16 + 8: return launch_fused_batch_t<5, 8>(segs, nseg, ents, progs, round, blocks, init_plus, s);
-    case 4 * 16 + 8: return launch_fused_batch_t<4, 8>(segs, nseg, ents, progs, round, blocks, init_plus, s);
-    case 5 * 16 + 7: return launch_fused_batch_t<5, 7>(segs, nseg, ents, progs, round, blocks, init_plus, s);
-    case 4 * 16 + 7: return launch_fused_batch_t<4, 7>(segs, nseg, ents, progs, round, blocks, init_plus, s);
-    case 5 * 16 + 9: return launch_fused_batch_t<5, 9>(segs, nseg, ents, progs, round, blocks, init_plus, s);
-    default: return hipErrorInvalidValue;
-    }
-}
 
 hipError_t launch_gather_batch(const BatchEntry *ents, uint64_t count, const uint64_t *xs,
                                uint64_t m, float2 *out, hipStream_t s) {
@@ -1197,25 +693,6 @@ bool fused_shape_supported(int R, int T) {
 }
 
 bool compiled_shape_supported(int R, int T) { return fused_shape_supported(R, T) || (R == 6 && T == 9); }
-
-hipError_t launch_fused(float2 *amps, int n, int R, int T, const PassProg &p, uint64_t branch,
-                        hipStream_t s) {
-    switch (R * 16 + T) {
-    case 5 * 16 + 8: return launch_fused_t<5, 8>(amps, n, p, branch, s);
-    case 5 * 16 + 7: return launch_fused_t<5, 7>(amps, n, p, branch, s);
-    case 4 * 16 + 7: return launch_fused_t<4, 7>(amps, n, p, branch, s);
-    case 4 * 16 + 6: return launch_fused_t<4, 6>(amps, n, p, branch, s);
-    case 3 * 16 + 6: return launch_fused_t<3, 6>(amps, n, p, branch, s);
-    case 3 * 16 + 4: return launch_fused_t<3, 4>(amps, n, p, branch, s);
-    case 2 * 16 + 3: return launch_fused_t<2, 3>(amps, n, p, branch, s);
-    case 4 * 16 + 8: return launch_fused_t<4, 8>(amps, n, p, branch, s);
-    case 6 * 16 + 8: return launch_fused_t<6, 8>(amps, n, p, branch, s);
-    case 5 * 16 + 9: return launch_fused_t<5, 9>(amps, n, p, branch, s);
-    case 4 * 16 + 9: return launch_fused_t<4, 9>(amps, n, p, branch, s);
-    case 6 * 16 + 7: return launch_fused_t<6, 7>(amps, n, p, branch, s);
-    default: return hipErrorInvalidValue;
-    }
-}
 
 hipError_t launch_plain_1q(float2 *amps, int n, int q, const float m[8], hipStream_t s) {
     const uint64_t pairs = 1ull << (n - 1);

@@ -38,11 +38,19 @@ void gates_in_range(const qsv_circuit &c, int lb, int le, std::vector<int> &idx)
     }
 }
 
-TileShape default_shape(int n) {
-    // (R, T) of the compiled kernels, largest tile first; the tuner may pick
-    // another one.  c low bits stay resident so every access is a run of
-    // 2^c amplitudes (2^c * 8 bytes).
+TileShape default_shape(int n, bool gate_order) {
+    // (R, T), largest tile first; the tuner may pick another one.  c low bits
+    // stay resident so every access is a run of 2^c amplitudes (2^c * 8 bytes).
     static const int shapes[][2] = {{5, 8}, {5, 7}, {4, 7}, {4, 6}, {3, 6}, {3, 4}, {2, 3}};
+    // Below 2^24 amplitudes the caches hold the state and a pass is bound by
+    // the instructions it issues and by the workgroups there are: 16 registers
+    // per thread and runs of 2^4 amplitudes keep the pass counts of the larger
+    // tile with twice the workgroups.  Generic kernel, (4, 8, 4) against
+    // (5, 8, 5): 16 qubits 25.9 / 33.6 us, 20 qubits depth 20 55.4 / 67.3, 23
+    // qubits 117 / 135; compiled passes 12.7 / 18.6, 30.3 / 40.4, 77.8 / 80.6.
+    // A call that keeps its rounding sequence (gate_order) keeps the tile that
+    // the sequence was defined on.
+    if (!gate_order && n >= 12 && n < 24) return {4, 8, 4};
     for (auto &s : shapes) {
         if (s[0] + s[1] <= n) {
             int c = std::min(5, s[1] + 1);

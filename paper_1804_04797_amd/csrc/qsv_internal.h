@@ -151,12 +151,15 @@ struct DenseKey {
     }
 };
 
+struct GenProg;  // genprog.h
+
 struct Plan {
     int n = 0, R = 0, T = 0, c = 0;
     bool oop = false;  // passes write a second buffer (free qubit-to-bit maps)
     std::vector<Pass> passes;
     std::vector<int> gate_range;  // indices of the gates in the layer range
     std::map<int, std::shared_ptr<void>> jit_variants;  // compiled kernels (jit.cpp)
+    std::shared_ptr<const std::vector<GenProg>> gen[2]; // lowered for the generic kernel: folded, in gate order
     std::mutex jit_mu;
 };
 
@@ -189,7 +192,7 @@ qsv_status generate_lattice_circuit(int rows, int cols, const uint8_t *present, 
 // works in place in the natural map.
 struct TileShape { int R, T, c; bool oop = false; };
 qsv_status build_plan(const qsv_circuit &c, int lb, int le, TileShape shape, Plan &out);
-TileShape default_shape(int n);
+TileShape default_shape(int n, bool gate_order = false);
 void gates_in_range(const qsv_circuit &c, int lb, int le, std::vector<int> &idx);
 
 // partition.cpp: the parts of a three-part partition and the combine's
