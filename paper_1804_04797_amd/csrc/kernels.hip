@@ -603,29 +603,66 @@ k_norm_small(const float2 *__restrict__ a, uint64_t dim, double *__restrict__ ou
     if (threadIdx.x == 0) *out = s[0];
 }
 
-// out[x] = sign[x] * sum_b A[b][x] * B[b][x]: 64 outputs per block, four
-// branch groups of 64 lanes each; FP64 products and sums, fixed order.
-__global__ void __launch_bounds__(256)
+// out[x] = sign[x] * sum_b A[b][x] * B[b][x]; FP64 products and sums, fixed
+// order.  Both tables are read once, so the read is the bound (33.6 MB for
+// 2048 branches of 1024 outputs); what it needs is loads in flight on every
+// CU.  A workgroup sums 2^lc columns; its threads split the branches (thread
+// t: column t mod 2^lc, branches t >> lc, + rows, ...), lanes of one column
+// add up across the wave, the waves through LDS.  Groups of neighbouring
+// columns go to one XCD (workgroups are dealt to the 8 XCDs in turn), so that
+// the workgroups that share a cache line share an L2.  With 64 columns and
+// four branch groups per workgroup, 16 workgroups in all, the table above
+// took 173 us; with 4 columns and 256 branch groups 10.7 us
+// with new tables each call (4096 x 4096 pairs: 38 us, 7.0 TB/s).
+__global__ void __launch_bounds__(1024)
 k_branch_combine(const float2 *__restrict__ A, const float2 *__restrict__ B, uint64_t nb,
-                 uint64_t m, const int8_t *__restrict__ sign, double2 *__restrict__ out) {
-    __shared__ double sr[4][64], si[4][64];
-    const int lane = threadIdx.x & 63, grp = threadIdx.x >> 6;
-    const uint64_t x = uint64_t(blockIdx.x) * 64 + lane;
+                 uint64_t m, const int8_t *__restrict__ sign, double2 *__restrict__ out, int lc) {
+    __shared__ double sr[1024], si[1024];  // [wave][column]
+    const uint32_t t = threadIdx.x, cols = 1u << lc, col = t & (cols - 1u);
+    const uint64_t rows = blockDim.x >> lc;
+    const uint32_t g = gridDim.x, blk = blockIdx.x;
+    const uint64_t group = (g % 8u == 0) ? uint64_t(blk % 8u) * (g / 8u) + blk / 8u : blk;
+    const uint64_t x = (group << lc) + col;
+    constexpr int U = 4;
     double ar = 0.0, ai = 0.0;
     if (x < m) {
-        for (uint64_t b = grp; b < nb; b += 4) {
-            const float2 p = A[b * m + x], q = B[b * m + x];
-            const double pr = p.x, pi = p.y, qr = q.x, qi = q.y;
-            ar += pr * qr - pi * qi;
-            ai += pr * qi + pi * qr;
+        for (uint64_t b0 = t >> lc; b0 < nb; b0 += U * rows) {
+            float2 p[U], q[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint64_t b = b0 + u * rows;
+                p[u] = q[u] = f2(0.f, 0.f);
+                if (b < nb) {
+                    p[u] = A[b * m + x];
+                    q[u] = B[b * m + x];
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (b0 + u * rows >= nb) break;
+                const double pr = p[u].x, pi = p[u].y, qr = q[u].x, qi = q[u].y;
+                ar += pr * qr - pi * qi;
+                ai += pr * qi + pi * qr;
+            }
         }
     }
-    sr[grp][lane] = ar;
-    si[grp][lane] = ai;
+    for (uint32_t off = 32; off >= cols; off >>= 1) {
+        ar += __shfl_xor(ar, int(off), 64);
+        ai += __shfl_xor(ai, int(off), 64);
+    }
+    // per wave one sum of each of its columns (a wave holds cols <= 64 of them)
+    const uint32_t wave = t >> 6, lane = t & 63u;
+    if (lane < cols) {
+        sr[(wave << lc) + lane] = ar;
+        si[(wave << lc) + lane] = ai;
+    }
     __syncthreads();
-    if (grp == 0 && x < m) {
-        double r = (sr[0][lane] + sr[1][lane]) + (sr[2][lane] + sr[3][lane]);
-        double i = (si[0][lane] + si[1][lane]) + (si[2][lane] + si[3][lane]);
+    if (t < cols && x < m) {
+        double r = 0.0, i = 0.0;
+        for (uint32_t w = 0; w < blockDim.x >> 6; ++w) {
+            r += sr[(w << lc) + t];
+            i += si[(w << lc) + t];
+        }
         if (sign && sign[x] < 0) { r = -r; i = -i; }
         out[x] = make_double2(r, i);
     }
@@ -817,8 +854,14 @@ hipError_t launch_sum_partials(const double *part, uint64_t count, double *out, 
 hipError_t launch_branch_combine(const float2 *A, const float2 *B, uint64_t nb, uint64_t m,
                                  const int8_t *sign, double2 *out, hipStream_t s) {
     if (m == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_branch_combine, dim3(unsigned((m + 63) / 64)), dim3(256), 0, s, A, B, nb,
-                       m, sign, out);
+    // fewer columns per workgroup until there is a workgroup per CU, as long
+    // as the branches give the freed threads something to add
+    int lc = 6;
+    while (lc > 0 && ((m + (1ull << lc) - 1) >> lc) < 256 && (1024u >> lc) < nb) --lc;
+    unsigned threads = 64;
+    while (threads < 1024 && (threads >> lc) < nb) threads *= 2;
+    hipLaunchKernelGGL(k_branch_combine, dim3(unsigned((m + (1ull << lc) - 1) >> lc)), dim3(threads), 0, s, A, B, nb,
+                       m, sign, out, lc);
     return hipGetLastError();
 }
 
