@@ -5,25 +5,36 @@
 // for a circuit cut into sides A and B (circuit_split): x_A / x_B are the
 // bits of x on the two sides, A_b / B_b the branch states of the halves and
 // s(x) = (-1)^{sum over folded pairs x_a x_b}.  As matrices, Psi = Ahat Bhat^T
-// with Ahat[x_A][b] = A_b[x_A], a complex GEMM of shape 2^nA x 2^nB x nb.  It
-// runs as two real GEMMs over an interleaved K index k = 2b + part:
-//   Mr = sum_k A1[k] B1[k],  A1 = (Ar, -Ai),  B1 = (Br, Bi)
-//   Mi = sum_k A2[k] B1[k],  A2 = (Ai,  Ar)
+// with Ahat[x_A][b] = A_b[x_A], a complex GEMM of shape 2^nA x 2^nB x nb.
+//
 // The default form sums the branch products in FP64: the FP32 inputs are
 // widened and multiplied on v_mfma_f64_16x16x4f64, so every product is exact
-// and every partial sum is an FP64 sum; the result is rounded once, to the
-// complex64 state or not at all for a complex128 output.  The FP32 form
-// (v_mfma_f32_16x16x4f32, FP32 accumulation) runs at twice the matrix-core
-// rate and is selected explicitly.  A workgroup owns a 128 x 128 output tile:
-// the FP32 form's four waves a 64 x 64 quadrant each (4 x 4 MFMA blocks for
-// each of Mr, Mi), the FP64 form's eight waves a 64 x 32 part each (4 x 2
-// blocks).  Branch chunks of 16 are staged in LDS as
-// k-major planes; the next chunk's global loads are issued before the current
-// chunk's MFMA work so that they overlap it.  The epilogue applies s(x) and
-// scatters the tile to the state's natural index order through per-tile
-// tables of the rows' and columns' output bits.  A launch covers one
-// block of rows and columns (CombineArgs): the whole matrix for a two-part
-// split, one value of the selector qubits for a three-part partition.
+// and every partial sum an FP64 sum, rounded once, to the complex64 state or
+// not at all for a complex128 one.  Three real products make a complex one,
+//   P = Ar Br, Q = Ai Bi, S = (Ar + Ai)(Br + Bi):  re = P - Q, im = S - P - Q
+// (the sums of two widened FP32 values are exact but for exponents 29 apart),
+// a quarter less matrix-core work than four.  The error of a complex64 state
+// is its one rounding either way (2.5e-8 for 2^15 x 2^15 x 1024); a sum of
+// 1024 branches in FP64 is 1.4e-15 off (relative, in the 2-norm) where four
+// products are 1.3e-15 off, as P, Q and S are sums of half as many terms.
+// Non-finite inputs give non-finite outputs, of whichever kind.  The FP32
+// form (v_mfma_f32_16x16x4f32, FP32 accumulation, selected explicitly) keeps
+// four products: there the cancellation in S - P - Q would show.
+//
+// The matrix cores bound all of it (a complex64 state is written once, the
+// branch tables are read from the caches), so a workgroup owns a large tile:
+// 128 x 128 outputs, eight waves with a 64 x 32 part each in FP64: 104.0 ms
+// for 2^15 x 2^15 x 1024, 63.4 TFLOP/s on the matrix cores (four products:
+// 131.6 ms, 66.8 TFLOP/s).  A small matrix has few such tiles (2^8 x 2^8:
+// four); below a tile for every CU it is cut into 32 x 32 tiles of four waves
+// (2^8 x 2^8 x 500: 255 us, now 25).  Branch chunks are staged in LDS as real and imaginary planes whose rows are 16 banks apart (an
+// operand read covers two rows at a time); the next chunk's global loads are
+// issued before the current chunk's MFMA work so that they overlap it.  The
+// epilogue applies s(x) and scatters the tile to the state's natural index
+// order through per-tile tables of the rows' and columns' output bits.  A
+// launch covers one block of rows and columns (CombineArgs): the whole matrix
+// for a two-part split, one value of the selector qubits for a three-part
+// partition.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -38,123 +49,125 @@ namespace {
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef double v4d __attribute__((ext_vector_type(4)));
 
-constexpr int kTile = 128;  // output rows (x_A) and columns (x_B) per workgroup
-constexpr int kBr = 16;     // branches per LDS chunk
-constexpr int kK = 2 * kBr; // interleaved K per chunk
 
-// F64: FP64 products and sums on eight waves (each a 64 x 32 part of the
-// tile: 128 accumulator registers per lane, so two waves share a SIMD and
-// one's staging hides behind the other's matrix work); otherwise FP32
-// accumulation on four waves (each a 64 x 64 quadrant; two workgroups per
-// CU).  out_c128: the output state is complex128.
-template <bool F64>
-__global__ void __launch_bounds__(F64 ? 512 : 256, F64 ? 1 : 2)
+// WR x WC waves, each MB x NB blocks of 16 x 16 outputs; kBr branches per LDS
+// chunk; WPE waves per SIMD (bounds the registers).
+template <bool F64, int MB, int NB, int WR, int WC, int kBr, int WPE>
+__global__ void __launch_bounds__(64 * WR * WC, WPE)
 k_combine_gemm(const float2 *__restrict__ A, const float2 *__restrict__ B, uint64_t nbr,
                const CombineArgs P, void *__restrict__ out, int out_c128) {
+    using Real = typename std::conditional<F64, double, float>::type;
     using Acc = typename std::conditional<F64, v4d, v4f>::type;
-    constexpr int NTH = F64 ? 512 : 256;  // threads
-    constexpr int NC = F64 ? 2 : 4;       // 16-column blocks per wave
-    __shared__ __attribute__((aligned(16))) float a1[kK][kTile];  // also the epilogue's 64-bit tables
-    __shared__ float a2[kK][kTile], b1[kK][kTile];
+    constexpr int NTH = 64 * WR * WC, TM = 16 * MB * WR, TN = 16 * NB * WC;
+    constexpr int NA = F64 ? 3 : 2;  // accumulators of a block: P, Q, S or re, im
+    __shared__ __attribute__((aligned(16))) float ar[kBr][TM + 16];
+    __shared__ float ai[kBr][TM + 16], br[kBr][TN + 16], bi[kBr][TN + 16];
+    __shared__ uint64_t rowx[TM], rowf[TM], colx[TN];
     const uint32_t t = threadIdx.x, lane = t & 63u, w = t >> 6;
-    const uint64_t i0 = uint64_t(blockIdx.x) * kTile, j0 = uint64_t(blockIdx.y) * kTile;
-    // this wave's part: rows wr * 64 + [0, 64), columns wc * 16 NC + [0, 16 NC)
-    const uint32_t wr = w & 1u, wc = w >> 1;
+    const uint64_t i0 = uint64_t(blockIdx.x) * TM, j0 = uint64_t(blockIdx.y) * TN;
+    // this wave's part: rows rw + [0, 16 MB), columns cw + [0, 16 NB)
+    const uint32_t rw = (w % WR) * 16 * MB, cw = (w / WR) * 16 * NB;
     const uint32_t lr = lane & 15u, lk = lane >> 4;
-    Acc accr[4][NC], acci[4][NC];
+    Acc acc[MB][NB][NA];
 #pragma unroll
-    for (int m = 0; m < 4; ++m)
+    for (int m = 0; m < MB; ++m)
 #pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            accr[m][c] = Acc{0, 0, 0, 0};
-            acci[m][c] = Acc{0, 0, 0, 0};
-        }
-    // staging: thread t always loads in-tile row tr of branches tb, tb + BS,
-    // ... of a chunk, so one pointer per side and a uniform stride address them
-    constexpr int BS = NTH / kTile;          // branches staged at once
-    constexpr int kPer = kBr * kTile / NTH;  // staged elements per thread and side
-    static_assert(kTile == 128 && kPer * BS == kBr, "staging covers a chunk");
-    const uint32_t tb = t >> 7, tr = t & 127u;
-    const float2 *pa = A + P.a_off + tb * P.a_stride + i0 + tr;
-    const float2 *pb = B + P.b_off + tb * P.b_stride + j0 + tr;
-    const uint64_t sa = BS * P.a_stride, sb = BS * P.b_stride;
-    float2 na_[kPer], nb_[kPer];
+        for (int c = 0; c < NB; ++c)
+#pragma unroll
+            for (int q = 0; q < NA; ++q) acc[m][c][q] = Acc{0, 0, 0, 0};
+    // staging: thread t always loads one in-tile row of every BS-th branch
+    constexpr int BA = NTH / TM, BB = NTH / TN;  // branches staged at once
+    constexpr int PA = kBr / BA, PB = kBr / BB;  // staged elements per thread
+    static_assert(BA * TM == NTH && BB * TN == NTH && PA * BA == kBr && PB * BB == kBr, "staging covers a chunk");
+    const uint32_t ba = t / TM, ra = t % TM, bb = t / TN, rb = t % TN;
+    const float2 *pa = A + P.a_off + ba * P.a_stride + i0 + ra;
+    const float2 *pb = B + P.b_off + bb * P.b_stride + j0 + rb;
+    const uint64_t sa = BA * P.a_stride, sb = BB * P.b_stride;
+    float2 na_[PA], nb_[PB];
     auto fetch = [&](uint64_t b0) {
 #pragma unroll
-        for (int q = 0; q < kPer; ++q) {
+        for (int q = 0; q < PA; ++q) {
             na_[q] = make_float2(0.f, 0.f);
+            if (b0 + ba + BA * q < nbr) na_[q] = pa[q * sa];
+        }
+#pragma unroll
+        for (int q = 0; q < PB; ++q) {
             nb_[q] = make_float2(0.f, 0.f);
-            if (b0 + tb + BS * q < nbr) {
-                na_[q] = pa[q * sa];
-                nb_[q] = pb[q * sb];
-            }
+            if (b0 + bb + BB * q < nbr) nb_[q] = pb[q * sb];
         }
         pa += kBr * P.a_stride;
         pb += kBr * P.b_stride;
+    };
+    auto mfma = [](Real a, Real b, Acc c) {
+        if constexpr (F64) return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+        else return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
     };
     fetch(0);
     for (uint64_t b0 = 0; b0 < nbr; b0 += kBr) {
         __syncthreads();  // previous chunk's fragments are read
 #pragma unroll
-        for (int q = 0; q < kPer; ++q) {
-            const uint32_t b = tb + BS * q;
-            a1[2 * b][tr] = na_[q].x;
-            a1[2 * b + 1][tr] = -na_[q].y;
-            a2[2 * b][tr] = na_[q].y;
-            a2[2 * b + 1][tr] = na_[q].x;
-            b1[2 * b][tr] = nb_[q].x;
-            b1[2 * b + 1][tr] = nb_[q].y;
+        for (int q = 0; q < PA; ++q) {
+            ar[ba + BA * q][ra] = na_[q].x;
+            ai[ba + BA * q][ra] = na_[q].y;
+        }
+#pragma unroll
+        for (int q = 0; q < PB; ++q) {
+            br[bb + BB * q][rb] = nb_[q].x;
+            bi[bb + BB * q][rb] = nb_[q].y;
         }
         __syncthreads();
         if (b0 + kBr < nbr) fetch(b0 + kBr);  // in flight during the MFMA work
 #pragma unroll
-        for (int ks = 0; ks < kK; ks += 4) {
-            float fa1[4], fa2[4], fb[NC];
+        for (int ks = 0; ks < kBr; ks += 4) {
+            Real fr[MB], fi[MB], gr[NB], gi[NB];
 #pragma unroll
-            for (int m = 0; m < 4; ++m) {
-                fa1[m] = a1[ks + lk][wr * 64 + m * 16 + lr];
-                fa2[m] = a2[ks + lk][wr * 64 + m * 16 + lr];
+            for (int m = 0; m < MB; ++m) {
+                fr[m] = Real(ar[ks + lk][rw + m * 16 + lr]);
+                fi[m] = Real(ai[ks + lk][rw + m * 16 + lr]);
             }
 #pragma unroll
-            for (int c = 0; c < NC; ++c) fb[c] = b1[ks + lk][wc * 16 * NC + c * 16 + lr];
+            for (int c = 0; c < NB; ++c) {
+                gr[c] = Real(br[ks + lk][cw + c * 16 + lr]);
+                gi[c] = Real(bi[ks + lk][cw + c * 16 + lr]);
+            }
             if constexpr (F64) {
-                double da1[4], da2[4], db[NC];
+                Real fs[MB], gs[NB];
 #pragma unroll
-                for (int m = 0; m < 4; ++m) {
-                    da1[m] = double(fa1[m]);
-                    da2[m] = double(fa2[m]);
-                }
+                for (int m = 0; m < MB; ++m) fs[m] = fr[m] + fi[m];
 #pragma unroll
-                for (int c = 0; c < NC; ++c) db[c] = double(fb[c]);
+                for (int c = 0; c < NB; ++c) gs[c] = gr[c] + gi[c];
 #pragma unroll
-                for (int m = 0; m < 4; ++m)
+                for (int m = 0; m < MB; ++m)
 #pragma unroll
-                    for (int c = 0; c < NC; ++c) {
-                        accr[m][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(da1[m], db[c], accr[m][c], 0, 0, 0);
-                        acci[m][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(da2[m], db[c], acci[m][c], 0, 0, 0);
+                    for (int c = 0; c < NB; ++c) {
+                        acc[m][c][0] = mfma(fr[m], gr[c], acc[m][c][0]);
+                        acc[m][c][1] = mfma(fi[m], gi[c], acc[m][c][1]);
+                        acc[m][c][NA - 1] = mfma(fs[m], gs[c], acc[m][c][NA - 1]);
                     }
             } else {
 #pragma unroll
-                for (int m = 0; m < 4; ++m)
+                for (int m = 0; m < MB; ++m)
 #pragma unroll
-                    for (int c = 0; c < NC; ++c) {
-                        accr[m][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa1[m], fb[c], accr[m][c], 0, 0, 0);
-                        acci[m][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa2[m], fb[c], acci[m][c], 0, 0, 0);
+                    for (int c = 0; c < NB; ++c) {
+                        acc[m][c][0] = mfma(fr[m], gr[c], acc[m][c][0]);
+                        acc[m][c][1] = mfma(fi[m], gr[c], acc[m][c][1]);
+                    }
+#pragma unroll
+                for (int m = 0; m < MB; ++m)
+#pragma unroll
+                    for (int c = 0; c < NB; ++c) {
+                        acc[m][c][0] = mfma(-fi[m], gi[c], acc[m][c][0]);
+                        acc[m][c][1] = mfma(fr[m], gi[c], acc[m][c][1]);
                     }
             }
         }
     }
     // epilogue: block (m, c) element r of this lane is row 4*lk + r (FP32
-    // accumulators) or row 4*r + lk (FP64 accumulators), column lr.
-    // The output bits of the tile's 128 rows and 128 columns and the sign mask
-    // of each row are tabulated once in the (now free) LDS staging area.
-    __syncthreads();  // last chunk's fragments are read
-    uint64_t *rowx = reinterpret_cast<uint64_t *>(&a1[0][0]);
-    uint64_t *rowf = rowx + kTile;
-    uint64_t *colx = rowf + kTile;
-    if (t < 256) {
-        const uint32_t k = t & 127u;
-        if (t < 128) {
+    // accumulators) or row 4*r + lk (FP64 accumulators), column lr.  The
+    // output bits of the tile's rows and columns and the sign mask of each
+    // row are tabulated once.
+    for (uint32_t k = t; k < uint32_t(TM + TN); k += NTH) {
+        if (k < uint32_t(TM)) {
             const uint64_t i = P.row_base + i0 + k;
             uint64_t x = 0, f = 0;
             for (int q = 0; q < P.na; ++q)
@@ -164,36 +177,49 @@ k_combine_gemm(const float2 *__restrict__ A, const float2 *__restrict__ B, uint6
             rowx[k] = x;
             rowf[k] = f;
         } else {
-            const uint64_t j = P.col_base + j0 + k;
+            const uint64_t j = P.col_base + j0 + (k - TM);
             uint64_t x = 0;
             for (int q = 0; q < P.nb; ++q)
                 if ((j >> q) & 1ull) x |= 1ull << P.pos_b[q];
-            colx[k] = x;
+            colx[k - TM] = x;
         }
     }
     __syncthreads();
-    const uint64_t j0b = P.col_base + j0;
-    uint64_t xb[NC];
+    uint64_t xb[NB];
 #pragma unroll
-    for (int c = 0; c < NC; ++c) xb[c] = colx[wc * 16 * NC + c * 16 + lr];
+    for (int c = 0; c < NB; ++c) xb[c] = colx[cw + c * 16 + lr];
 #pragma unroll
-    for (int m = 0; m < 4; ++m) {
+    for (int m = 0; m < MB; ++m) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const uint32_t il = wr * 64 + m * 16 + (F64 ? 4 * r + lk : 4 * lk + r);
-            const uint64_t xa = rowx[il], fm = rowf[il] & j0b;
-            const uint32_t fl = uint32_t(rowf[il]) & 127u;
+            const uint32_t il = rw + m * 16 + (F64 ? 4 * r + lk : 4 * lk + r);
+            const uint64_t xa = rowx[il], fm = rowf[il];
 #pragma unroll
-            for (int c = 0; c < NC; ++c) {
-                const uint32_t jl = wc * 16 * NC + c * 16 + lr;
-                const bool neg = ((__popcll(fm) + __popc(fl & jl)) & 1) != 0;
-                double vr = double(accr[m][c][r]), vi = double(acci[m][c][r]);
-                if (neg) { vr = -vr; vi = -vi; }
+            for (int c = 0; c < NB; ++c) {
+                const uint64_t j = P.col_base + j0 + cw + c * 16 + lr;
+                double vr, vi;
+                if constexpr (F64) {
+                    vr = acc[m][c][0][r] - acc[m][c][1][r];
+                    vi = acc[m][c][NA - 1][r] - acc[m][c][0][r] - acc[m][c][1][r];
+                } else {
+                    vr = double(acc[m][c][0][r]);
+                    vi = double(acc[m][c][1][r]);
+                }
+                if (__popcll(fm & j) & 1) { vr = -vr; vi = -vi; }
                 if (out_c128) static_cast<double2 *>(out)[xa | xb[c]] = make_double2(vr, vi);
                 else static_cast<float2 *>(out)[xa | xb[c]] = make_float2(float(vr), float(vi));
             }
         }
     }
+}
+
+template <bool F64, int MB, int NB, int WR, int WC, int kBr, int WPE>
+hipError_t launch_gemm(const float2 *X, const float2 *Y, uint64_t nbr, const CombineArgs &Q, void *out, bool out_c128,
+                       hipStream_t s) {
+    const dim3 grid(unsigned((1ull << Q.na_blk) / (16 * MB * WR)), unsigned((1ull << Q.nb_blk) / (16 * NB * WC)));
+    hipLaunchKernelGGL((k_combine_gemm<F64, MB, NB, WR, WC, kBr, WPE>), grid, dim3(64 * WR * WC), 0, s, X, Y, nbr, Q, out,
+                       out_c128 ? 1 : 0);
+    return hipGetLastError();
 }
 
 // Leading local bits of a side that land on output bits 0, 1, 2, ... in order.
@@ -227,10 +253,17 @@ hipError_t launch_combine_gemm(const float2 *A, const float2 *B, uint64_t nbr, c
         std::memcpy(Q.fold_a, P.fold_b, sizeof(Q.fold_a));
         std::memcpy(Q.fold_b, P.fold_a, sizeof(Q.fold_b));
     }
-    const dim3 grid(unsigned(1ull << (Q.na_blk - 7)), unsigned(1ull << (Q.nb_blk - 7)));
-    if (fp64) hipLaunchKernelGGL(k_combine_gemm<true>, grid, dim3(512), 0, s, X, Y, nbr, Q, out, out_c128 ? 1 : 0);
-    else hipLaunchKernelGGL(k_combine_gemm<false>, grid, dim3(256), 0, s, X, Y, nbr, Q, out, out_c128 ? 1 : 0);
-    return hipGetLastError();
+    // 128 x 128 tiles when there is one for every CU, else 32 x 32 (500
+    // branches: 2^10 x 2^10 67 us against 205 on large tiles; 300 branches:
+    // 2^12 x 2^12 502 us on large tiles against 604).  Chunks of 8 branches
+    // keep the large tile's three sums per output in registers (104.0 ms for
+    // 2^15 x 2^15 x 1024; 106.3 with 16, which spills).
+    const bool large = Q.na_blk + Q.nb_blk >= 14 + 8;
+    if (!fp64)
+        return large ? launch_gemm<false, 4, 4, 2, 2, 16, 2>(X, Y, nbr, Q, out, out_c128, s)
+                     : launch_gemm<false, 1, 1, 2, 2, 32, 1>(X, Y, nbr, Q, out, out_c128, s);
+    return large ? launch_gemm<true, 4, 2, 2, 4, 8, 2>(X, Y, nbr, Q, out, out_c128, s)
+                 : launch_gemm<true, 1, 1, 2, 2, 32, 1>(X, Y, nbr, Q, out, out_c128, s);
 }
 
 }  // namespace qsv
