@@ -39,9 +39,9 @@ hipError_t launch_gather_c128(const void *amps, int n, const uint64_t *xs, uint6
 // sets *flag (mapped host memory) when some xs[k] >= 2^n
 hipError_t launch_check_range(const uint64_t *xs, uint64_t m, int n, unsigned int *flag, hipStream_t s);
 hipError_t launch_norm(const float2 *amps, int n, double *out, double *partials, hipStream_t s);
-// partial sums launch_norm writes for a state of 2^n amplitudes (at most 65536)
+// partial sums launch_norm writes for a state of 2^n amplitudes (at most 8192)
 size_t norm_partial_count(int n);
-// <a|b> in FP64 into out[0] (re), out[1] (im); partials: 2 * 65536 doubles
+// <a|b> in FP64 into out[0] (re), out[1] (im); partials: 2 * 8192 doubles
 hipError_t launch_dot(const float2 *a, const float2 *b, int n, double *out, double *partials,
                       hipStream_t s);
 // Full-state branch combine (combine.hip).  Local bit q of side A / B sits at
