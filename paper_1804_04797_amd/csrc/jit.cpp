@@ -490,6 +490,7 @@ struct Gen {
     int lds_elems = 0;       // largest staging buffer of the pass (elements)
     bool persistent = false; // generating the persistent (prefetching) form
     bool stage_whole = false; // one tile per workgroup, exchanges staged whole when they fit
+    bool batched_form = false; // states of a batch, one per grid row
     bool sample_rows = false; // sampling pass with one grid row per sibling branch
 
     uint32_t xweight(const XLayout &x, int q) const {
@@ -856,18 +857,24 @@ struct Gen {
         }
         o << "}\n";
     }
-    void emit_store(const std::vector<int> &tst) {
+    // Up to 2^25 amplitudes the stores are ordinary ones: the last-level cache
+    // keeps much of the state for the next pass (24 qubits, 3 passes: 174 ->
+    // 155 us; 25 qubits: 330 -> 288; 26 qubits, 4 passes: 829 -> 841).  A batch
+    // holds more than one state (2 x 1024 of 15 qubits: 330 -> 348).
+    void emit_store(const std::vector<int> &tst, int n) {
+        auto store = [&](const std::string &at) {
+            return n <= 25 && !batched_form ? "*(dst + " + at + ") = w;" : "__builtin_nontemporal_store(w, dst + " + at + ");";
+        };
         if (dp) {
             o << "{v2d* dst = (v2d*)(a + (bst | " << scatter_expr("t", tst, true) << "));\n";
             for (int j = 0; j < N; ++j)
-                o << "{const v2d w = {v[" << j << "].x,v[" << j << "].y};__builtin_nontemporal_store(w, dst + "
-                  << hex64(reg_offset(j, P.st_phys, 0)) << ");}\n";
+                o << "{const v2d w = {v[" << j << "].x,v[" << j << "].y};"
+                  << store(hex64(reg_offset(j, P.st_phys, 0))) << "}\n";
         } else {
             o << "{v4f* dst = (v4f*)(a + (bst | " << scatter_expr("t", tst, true) << "));\n";
             for (int j = 0; j < N; j += 2)
                 o << "{const v4f w = {v[" << j << "].x,v[" << j << "].y,v[" << j + 1 << "].x,v[" << j + 1
-                  << "].y};__builtin_nontemporal_store(w, dst + " << hex64(reg_offset(j, P.st_phys, 1) / 2)
-                  << ");}\n";
+                  << "].y};" << store(hex64(reg_offset(j, P.st_phys, 1) / 2)) << "}\n";
         }
         o << "}\n";
     }
@@ -1000,6 +1007,7 @@ struct Gen {
         sample_rows = sample && !tiles && init_kind < 0;
         uses_lds = false;
         persistent = loop;
+        batched_form = batched;
         for (int pc = 0; pc < P.n_ops; ++pc) {
             if ((P.ops[pc] & 0xff) == OP_XCHG) { uses_lds = true; ++pc; }
         }
@@ -1044,7 +1052,17 @@ struct Gen {
             if (init_kind >= 0) emit_init(init_kind, n, tld);
             else emit_load("v", "base", tld);
         } else if (!loop) {
-            o << "const unsigned long long tile = tile0 + blockIdx.x;\n";
+            // Workgroups are dealt to the 8 XCDs in turn.  From 2^27 amplitudes
+            // on each XCD walks an eighth of the tiles instead of every eighth
+            // tile, so that the pages it has open and translated are its own
+            // (28 qubits, 3 passes: 2637 -> 2378 us; 30 qubits, 5 passes: 16.26
+            // -> 15.53 ms; 26 qubits, 4 passes: 829 -> 846 us).
+            // The tile count is a literal: a gridDim in the expression changes how
+            // the compiler orders sums further down, and with it their rounding.
+            if (n >= 27)
+                o << "const unsigned long long tile = tile0 + (((blockIdx.x & 7u) << " << (n - L - 3)
+                  << ") + (blockIdx.x >> 3));\n";
+            else o << "const unsigned long long tile = tile0 + blockIdx.x;\n";
             o << "const unsigned long long base = " << scatter_expr("tile", glob, true) << ";\n";
             o << "const unsigned long long bst = " << scatter_expr("tile", globst, true) << ";\n";
             o << CT << " v[" << N << "];\n";
@@ -1081,7 +1099,7 @@ struct Gen {
         } else if (dot) {
             emit_dot(loop, tst);
         } else {
-            emit_store(tst);
+            emit_store(tst, n);
             if (norm) emit_norm(loop);
         }
         if (loop) o << "}\n";
