@@ -154,24 +154,6 @@ const qsv_fuse_opts *effective_opts(const qsv_circuit *c, const qsv_fuse_opts *o
     return nullptr;
 }
 
-qsv_status resolve_shape(const qsv_circuit *c, const qsv_fuse_opts *opts, TileShape &sh,
-                         bool gate_order = false) {
-    sh = default_shape(c->n, gate_order);
-    if (opts) {
-        if (opts->reg_qubits) sh.R = opts->reg_qubits;
-        if (opts->thread_qubits) sh.T = opts->thread_qubits;
-        if (opts->low_qubits) sh.c = opts->low_qubits;
-        else if (opts->reg_qubits || opts->thread_qubits) sh.c = std::min(5, sh.T + 1);
-    }
-    if (sh.R == 0) return QSV_OK;  // too small for a tile: plain path
-    if (!compiled_shape_supported(sh.R, sh.T))
-        return fail(QSV_EUNSUPPORTED, "no fused kernel compiled for this (reg, thread) shape");
-    if (sh.R + sh.T > c->n) return fail(QSV_EUNSUPPORTED, "tile larger than the state");
-    if (sh.c < 1 || sh.c - 1 > sh.T || sh.c > sh.R + sh.T)
-        return fail(QSV_EINVAL, "low_qubits out of range for the tile shape");
-    return QSV_OK;
-}
-
 // Out-of-place sweeps (compiled pass kernels only): opts->out_of_place
 // 1 = required, -1 = never, 0 = for states of 2^24 amplitudes or more.
 int oop_mode(const qsv_circuit *c, const qsv_fuse_opts *opts, int jm) {
@@ -250,6 +232,58 @@ qsv_status get_plan(const qsv_circuit *cc, int lb, int le, TileShape sh,
     return QSV_OK;
 }
 
+}  // namespace
+
+// Default tile of compiled passes from 2^24 amplitudes on: every pass streams
+// the state, so the tile with the fewest passes, at first the smaller one and
+// the longer runs (28 qubits depth 14: 4 passes on (5, 8, 5) 3284 us, 3 on
+// (5, 8, 4) 2649 and on (5, 9, 5) 2602; 26 qubits depth 24: 5 passes 985, 4 on
+// (5, 8, 4) 828; equal counts: (5, 8, 5) 170, (5, 9, 5) 192 at 24 qubits).
+// The choice is remembered by the gates' hash (two circuits with one hash would
+// share a tile that fits both), so that another handle of a circuit plans one
+// tile only.
+qsv_status compiled_default_shape(const qsv_circuit *c, int lb, int le, bool oop, TileShape &sh) {
+    if (c->n < 24) return QSV_OK;
+    static const int kTiles[][3] = {{5, 8, 5}, {5, 8, 4}, {5, 9, 5}, {5, 9, 4}};
+    static std::mutex mu;
+    static std::map<uint64_t, int> chosen;  // at most kKept entries
+    constexpr size_t kKept = 4096;
+    uint64_t h = 0xcbf29ce484222325ull;  // FNV-1a over 64-bit words
+    auto mix = [&h](uint64_t w) { h = (h ^ w) * 0x100000001b3ull; };
+    mix(uint64_t(c->n) | uint64_t(oop) << 8 | uint64_t(uint32_t(lb)) << 16 | uint64_t(uint16_t(le)) << 48);
+    for (const qsv_gate &g : c->gates) {
+        mix(uint64_t(g.kind) | uint64_t(g.q0) << 8 | uint64_t(g.q1) << 16 | uint64_t(g.arg) << 24 | uint64_t(g.layer) << 32);
+        h ^= h >> 29;
+    }
+    {
+        std::lock_guard<std::mutex> g(mu);
+        const auto it = chosen.find(h);
+        if (it != chosen.end()) {
+            const int *t = kTiles[it->second];
+            sh = TileShape{t[0], t[1], t[2]};
+            return QSV_OK;
+        }
+    }
+    size_t fewest = ~size_t(0);
+    int best = 0;
+    for (int k = 0; k < 4 && fewest > 1; ++k) {
+        const int *t = kTiles[k];
+        std::shared_ptr<Plan> plan;
+        const qsv_status st = get_plan(c, lb, le, TileShape{t[0], t[1], t[2], oop}, plan);
+        if (st != QSV_OK) return st;
+        if (plan->passes.size() >= fewest) continue;
+        fewest = plan->passes.size();
+        best = k;
+    }
+    sh = TileShape{kTiles[best][0], kTiles[best][1], kTiles[best][2]};
+    std::lock_guard<std::mutex> g(mu);
+    if (chosen.size() >= kKept) chosen.clear();
+    chosen[h] = best;
+    return QSV_OK;
+}
+
+namespace {
+
 // 0 = generic pass kernel; otherwise the kJit* flags the compiled kernels add
 int jit_mode(const qsv_circuit *c, const qsv_fuse_opts *opts) {
     int j = opts ? opts->jit : 0;
@@ -263,6 +297,30 @@ int jit_mode(const qsv_circuit *c, const qsv_fuse_opts *opts) {
     if (j == 3) return 1 | kJitPerPass | int((opts->pass_forms & ((1u << kJitPassBits) - 1u)) << 8);
     if (j == 4) return 1 | kJitWhole;
     return j >= 2 ? (1 | kJitLoop) : 1;
+}
+
+// Tile shape of a call: the options' one, else the default.
+qsv_status resolve_shape(const qsv_circuit *c, const qsv_fuse_opts *opts, TileShape &sh, int lb, int le,
+                         bool gate_order = false) {
+    sh = default_shape(c->n, gate_order);
+    const int jm = jit_mode(c, opts);
+    if (!gate_order && jm && !(opts && (opts->reg_qubits || opts->thread_qubits || opts->low_qubits))) {
+        const qsv_status st = compiled_default_shape(c, lb, le, oop_mode(c, opts, jm) != 0, sh);
+        if (st != QSV_OK) return st;
+    }
+    if (opts) {
+        if (opts->reg_qubits) sh.R = opts->reg_qubits;
+        if (opts->thread_qubits) sh.T = opts->thread_qubits;
+        if (opts->low_qubits) sh.c = opts->low_qubits;
+        else if (opts->reg_qubits || opts->thread_qubits) sh.c = std::min(5, sh.T + 1);
+    }
+    if (sh.R == 0) return QSV_OK;  // too small for a tile: plain path
+    if (!compiled_shape_supported(sh.R, sh.T))
+        return fail(QSV_EUNSUPPORTED, "no fused kernel compiled for this (reg, thread) shape");
+    if (sh.R + sh.T > c->n) return fail(QSV_EUNSUPPORTED, "tile larger than the state");
+    if (sh.c < 1 || sh.c - 1 > sh.T || sh.c > sh.R + sh.T)
+        return fail(QSV_EINVAL, "low_qubits out of range for the tile shape");
+    return QSV_OK;
 }
 
 void gate_matrix_f32(uint8_t kind, float m[8]) {
@@ -304,7 +362,7 @@ qsv_status time_sweep_passes(const qsv_circuit *c, int lb, int le, const qsv_fus
                              void *amps, void *workspace, size_t ws_bytes, hipStream_t s,
                              uint64_t max_tiles, std::vector<float> &ms) {
     TileShape sh;
-    qsv_status st = resolve_shape(c, opts, sh, true);
+    qsv_status st = resolve_shape(c, opts, sh, lb, le, true);
     if (st != QSV_OK) return st;
     const int jm = jit_mode(c, opts);
     if (sh.R == 0 || !jm) return fail(QSV_EUNSUPPORTED, "pass timing needs compiled pass kernels");
@@ -468,7 +526,7 @@ qsv_status sv_apply_fused(void *amps, const qsv_circuit *c, uint64_t branch, int
     opts = effective_opts(c, opts, layer_begin, layer_end, &tuned);
     if (opts && opts->plain) return sv_apply_plain(amps, c, branch, layer_begin, layer_end, stream);
     TileShape sh;
-    if ((st = resolve_shape(c, opts, sh)) != QSV_OK) return st;
+    if ((st = resolve_shape(c, opts, sh, layer_begin, layer_end)) != QSV_OK) return st;
     if (sh.R == 0) return sv_apply_plain(amps, c, branch, layer_begin, layer_end, stream);
     if ((st = check_device()) != QSV_OK) return st;
     std::shared_ptr<Plan> plan;
@@ -513,7 +571,7 @@ qsv_status sv_apply_fused_from(const void *src, void *dst, const qsv_circuit *c,
     TileShape sh;
     bool fused = !(opts && opts->plain);
     if (fused) {
-        if ((st = resolve_shape(c, opts, sh)) != QSV_OK) return st;
+        if ((st = resolve_shape(c, opts, sh, layer_begin, layer_end)) != QSV_OK) return st;
         fused = sh.R != 0;
     }
     const int jm = fused ? jit_mode(c, opts) : 0;
@@ -588,7 +646,7 @@ static qsv_status sampler_create(const qsv_circuit *c, int layer_begin, int laye
     const qsv_fuse_opts *eo = effective_opts(c, opts, layer_begin, layer_end, &tuned);
     bool fused = !(eo && eo->plain);
     if (fused) {
-        if ((st = resolve_shape(c, eo, S->sh)) != QSV_OK) return st;
+        if ((st = resolve_shape(c, eo, S->sh, layer_begin, layer_end)) != QSV_OK) return st;
         fused = S->sh.R != 0;
     }
     S->jm = fused ? jit_mode(c, eo) : 0;
@@ -1020,7 +1078,7 @@ qsv_status sv_simulate(void *amps, const qsv_circuit *c, uint64_t branch, int in
     TileShape sh;
     bool fused = !(opts && opts->plain);
     if (fused) {
-        if ((st = resolve_shape(c, opts, sh, true)) != QSV_OK) return st;
+        if ((st = resolve_shape(c, opts, sh, layer_begin, layer_end, true)) != QSV_OK) return st;
         fused = sh.R != 0;
     }
     std::shared_ptr<Plan> plan;
@@ -1104,7 +1162,7 @@ qsv_status sv_simulate_dot(void *amps, const qsv_circuit *c, uint64_t branch, in
     TileShape sh;
     bool fused = !(opts && opts->plain);
     if (fused) {
-        if ((st = resolve_shape(c, opts, sh, true)) != QSV_OK) return st;
+        if ((st = resolve_shape(c, opts, sh, layer_begin, layer_end, true)) != QSV_OK) return st;
         fused = sh.R != 0;
     }
     const int jm = fused ? jit_mode(c, opts) : 0;
@@ -1193,7 +1251,9 @@ qsv_status sv_workspace_bytes(const qsv_circuit *c, int layer_begin, int layer_e
     TileShape sh{0, 0, 0};
     const bool fused = !(opts && opts->plain);
     if (fused) {
-        qsv_status st = resolve_shape(c, opts, sh);
+        // (no default tile of 2^24 amplitudes or more is below 2^11: its size is
+        // the same for every tile, so none has to be planned here)
+        qsv_status st = resolve_shape(c, opts, sh, layer_begin, layer_end, true);
         if (st != QSV_OK) return st;
     }
     const int jm = (fused && sh.R) ? jit_mode(c, opts) : 0;
@@ -1210,7 +1270,7 @@ qsv_status sv_plan_info(const qsv_circuit *c, int layer_begin, int layer_end,
     qsv_fuse_opts tuned;
     opts = effective_opts(c, opts, layer_begin, layer_end, &tuned);
     TileShape sh;
-    qsv_status st = resolve_shape(c, opts, sh);
+    qsv_status st = resolve_shape(c, opts, sh, layer_begin, layer_end);
     if (st != QSV_OK) return st;
     if (sh.R == 0) return fail(QSV_EUNSUPPORTED, "sv_plan_info: state too small for a tile");
     std::shared_ptr<Plan> plan;
@@ -1246,7 +1306,7 @@ qsv_status sv_debug_emulate(void *amps_host, const qsv_circuit *c, uint64_t bran
     qsv_fuse_opts tuned;
     opts = effective_opts(c, opts, layer_begin, layer_end, &tuned);
     TileShape sh;
-    qsv_status st = resolve_shape(c, opts, sh);
+    qsv_status st = resolve_shape(c, opts, sh, layer_begin, layer_end);
     if (st != QSV_OK) return st;
     if (sh.R == 0) return fail(QSV_EUNSUPPORTED, "sv_debug_emulate: state too small for a tile");
     std::shared_ptr<Plan> plan;
@@ -1287,7 +1347,7 @@ qsv_status sv_debug_jit_compile(const qsv_circuit *c, int layer_begin, int layer
     qsv_fuse_opts tuned;
     opts = effective_opts(c, opts, layer_begin, layer_end, &tuned);
     TileShape sh;
-    qsv_status st = resolve_shape(c, opts, sh);
+    qsv_status st = resolve_shape(c, opts, sh, layer_begin, layer_end);
     if (st != QSV_OK) return st;
     if (sh.R == 0) return fail(QSV_EUNSUPPORTED, "sv_debug_jit_compile: state too small for a tile");
     std::shared_ptr<Plan> plan;
