@@ -46,16 +46,28 @@ k_gather_batch(const BatchEntry *__restrict__ ents, uint64_t count, const uint64
 // with v_mfma_f32_16x16x4_f32 (four real products; wave w owns 16-row output
 // blocks), write Y back through LDS and store it in place.
 // ---------------------------------------------------------------------------
+// 32-bit words only: the kernels read them with scalar loads.  (Read as bytes,
+// the tile's origin was a chain of vector loads per tile, one per bit, whose
+// waits also waited for the next tile's loads: 24 qubits, k = 4, 5, 6, 7: 63.8,
+// 61.1, 96.5, 159.3 us per block, now 43.6, 51.7, 84.9, 144.4; k = 4 is bound by
+// the state's traffic, 6.2 TB/s, k = 7 by the matrix cores, 119 TFLOP/s.)
 struct DenseArgs {
     uint64_t tiles;
-    uint8_t glob_bits[48];     // tile index bit i -> physical bit
-    uint8_t phys[16];          // tile local bit i -> physical bit
-    uint8_t sub[16];           // position of local bit i within the row or column index
-    uint8_t sub_row[8];        // row index bit b -> tile local bit
-    uint8_t sub_col[8];        // column index bit b -> tile local bit
-    uint16_t rowmask;          // local bits that belong to the row index
-    int32_t n_glob;
+    uint32_t run[20];          // tile index -> origin: bits [src, src + len) to bit dst (src | len << 8 | dst << 16)
+    uint32_t n_runs;
+    uint32_t phys[16];         // tile local bit i -> physical bit
+    uint32_t sub[16];          // position of local bit i within the row or column index
+    uint32_t rowmask;          // local bits that belong to the row index
 };
+
+__device__ __forceinline__ uint64_t dense_origin(const DenseArgs &A, uint64_t tile) {
+    uint64_t base = 0;
+    for (uint32_t r = 0; r < A.n_runs; ++r) {
+        const uint32_t x = A.run[r];
+        base |= ((tile >> (x & 0xffu)) & ((1ull << ((x >> 8) & 0xffu)) - 1ull)) << (x >> 16);
+    }
+    return base;
+}
 
 template <int K>
 __global__ void __launch_bounds__(256)
@@ -85,8 +97,7 @@ k_dense(float2 *__restrict__ amps, const float *__restrict__ mat_t, const DenseA
     const uint32_t rb0 = (w * NB) / 4;       // row block of this wave
     const uint32_t cb0 = (w * NB) % 4;       // first column block
     for (uint64_t tile = blockIdx.x; tile < A.tiles; tile += gridDim.x) {
-        uint64_t base = 0;
-        for (int i = 0; i < A.n_glob; ++i) base |= ((tile >> i) & 1ull) << A.glob_bits[i];
+        const uint64_t base = dense_origin(A, tile);
         __syncthreads();  // previous tile's LDS reads are complete
 #pragma unroll
         for (int it = 0; it < PER; ++it) {
@@ -232,21 +243,16 @@ k_dense_strip(float2 *__restrict__ amps, const float *__restrict__ mat_t, const 
     const bool b0row = (A.rowmask & 1u) != 0;
     const uint32_t b0 = 1u << A.sub[0];
     v4f nx[PER];
-    auto tile_base = [&](uint64_t tile) {
-        uint64_t base = 0;
-        for (int i = 0; i < A.n_glob; ++i) base |= ((tile >> i) & 1ull) << A.glob_bits[i];
-        return base;
-    };
-    auto fetch = [&](uint64_t tile) {
-        const uint64_t base = tile_base(tile);
+    auto fetch = [&](uint64_t base) {
 #pragma unroll
         for (int it = 0; it < PER; ++it)
             nx[it] = __builtin_nontemporal_load(reinterpret_cast<const v4f *>(amps + (base | off_t | off_it(it))));
     };
     uint64_t tile = blockIdx.x;
-    if (tile < A.tiles) fetch(tile);
+    uint64_t next = dense_origin(A, tile);
+    if (tile < A.tiles) fetch(next);
     for (; tile < A.tiles; tile += gridDim.x) {
-        const uint64_t base = tile_base(tile);
+        const uint64_t base = next;
         __syncthreads();  // the previous tile's LDS reads are complete
 #pragma unroll
         for (int it = 0; it < PER; ++it) {
@@ -259,7 +265,8 @@ k_dense_strip(float2 *__restrict__ amps, const float *__restrict__ mat_t, const 
             xi[p1] = nx[it].w;
         }
         __syncthreads();
-        if (tile + gridDim.x < A.tiles) fetch(tile + gridDim.x);  // in flight during the MFMA work
+        next = dense_origin(A, tile + gridDim.x);
+        if (tile + gridDim.x < A.tiles) fetch(next);  // in flight during the MFMA work
         v4f arr[4], aii[4], ai[4];
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
@@ -334,32 +341,30 @@ hipError_t launch_dense_t(float2 *amps, int n, const int *qubits, const float *m
     for (int q = 0, c = 0; q < n && c < 6; ++q)
         if (!((qmask >> q) & 1)) { cmask |= 1ull << q; ++c; }
     const uint64_t res = qmask | cmask;
-    int li = 0, ri = 0, ci = 0;
+    int li = 0, ci = 0;
     for (int q = 0; q < n; ++q) {
         if (!((res >> q) & 1)) continue;
-        A.phys[li] = uint8_t(q);
+        A.phys[li] = uint32_t(q);
         if ((qmask >> q) & 1) {
-            A.rowmask |= uint16_t(1u << li);
+            A.rowmask |= 1u << li;
             // row index bit = position of q in the block's qubit list
             int pos = 0;
             while (qubits[pos] != q) ++pos;
-            A.sub[li] = uint8_t(pos);
-            ++ri;
+            A.sub[li] = uint32_t(pos);
         } else {
-            A.sub[li] = uint8_t(ci++);
+            A.sub[li] = uint32_t(ci++);
         }
         ++li;
     }
-    int g = 0;
-    for (int q = 0; q < n; ++q)
-        if (!((res >> q) & 1)) A.glob_bits[g++] = uint8_t(q);
-    A.n_glob = g;
-    A.tiles = 1ull << (n - K - 6);
-    (void)ri;
-    for (int l = 0; l < K + 6; ++l) {
-        if ((A.rowmask >> l) & 1u) A.sub_row[A.sub[l]] = uint8_t(l);
-        else A.sub_col[A.sub[l]] = uint8_t(l);
+    for (int q = 0, src = 0; q < n;) {  // runs of non-resident bits
+        if ((res >> q) & 1) { ++q; continue; }
+        int e = q;
+        while (e < n && !((res >> e) & 1)) ++e;
+        A.run[A.n_runs++] = uint32_t(src) | uint32_t(e - q) << 8 | uint32_t(q) << 16;
+        src += e - q;
+        q = e;
     }
+    A.tiles = 1ull << (n - K - 6);
     if constexpr (K >= 6) {
         return launch_dense_strip_t<K>(amps, mat_t, A, s);
     } else {
