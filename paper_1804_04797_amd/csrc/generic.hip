@@ -251,8 +251,10 @@ __device__ __forceinline__ float2 omega(uint32_t k) {
     return make_float2(x, y);
 }
 
-template <int R, int T>
-__device__ __forceinline__ void run_tile(const GenProg &P, const TileArgs &A, float2 *lds) {
+// HALF: exchanges stage the real parts, then the imaginary parts: half the
+// buffer, so twice the workgroups on a CU, for twice the barriers.
+template <int R, int T, bool HALF>
+__device__ __forceinline__ void run_tile(const GenProg &P, const TileArgs &A, float *lds) {
     constexpr int N = 1 << R;
     constexpr GenWeights W = gen_weights(R, T);
     const uint32_t t = threadIdx.x;
@@ -305,24 +307,25 @@ __device__ __forceinline__ void run_tile(const GenProg &P, const TileArgs &A, fl
     uint32_t e = 0;
 
     auto parity = [](uint32_t x) { return uint32_t(__popc(x)) & 1u; };
-    // sign bit of an operand: thread, tile and branch partners
-    auto coef = [&](uint32_t f, uint32_t tm, uint32_t gm, uint32_t extra) {
-        const uint32_t uni = ((f & 8u) ? 0x3f3504f3u : 0x3f800000u) ^ ((parity(gm & tile) ^ ((f >> 5) & 1u) ^ extra) << 31);
+    // coefficient of an operand: the sign from the thread and tile partners
+    auto coef = [&](uint32_t bits, uint32_t tm, uint32_t gm) {
+        const uint32_t uni = bits ^ (uint32_t(__popc(gm & tile)) << 31);
         return __uint_as_float(uni ^ (uint32_t(__popc(tm & t)) << 31));
     };
+    uint32_t extra = 0;  // sign bit for the next op (GEN_ZB)
     GenOp nx = P.ops[0];
     for (uint32_t pc = 0;; ++pc) {
         const GenOp op = nx;
         const uint32_t code = op.w[0] & 0xffu;
         if (code == GEN_END) break;
         nx = P.ops[pc + 1];
-        const uint32_t zsign = parity(op.w[6] & uint32_t(A.branch)) ^ parity(op.w[7] & uint32_t(A.branch >> 32));
         if (code < GEN_LSWAP4 || (code >= GEN_HI && code < GEN_T)) {
             const uint32_t f0 = (op.w[0] >> 8) & 0xffu, f1 = (op.w[0] >> 16) & 0xffu;
             if (f0 & 0x58u) v.diagonal(f0, op.w[1]);
             if (f1 & 0x58u) v.diagonal(f1, op.w[2]);
-            const float c = coef(f0, op.w[3] & 0xffffu, op.w[4], zsign);
-            const float d = coef(f1, op.w[3] >> 16, op.w[5], 0u);
+            const float c = coef(op.w[6] ^ extra, op.w[3] & 0xffffu, op.w[4]);
+            const float d = coef(op.w[7], op.w[3] >> 16, op.w[5]);
+            extra = 0;
             switch (code) {
 #define QSV_H1(S) case GEN_H1 + S: v.template h1<S>(c); break;
             QSV_H1(0) QSV_H1(1) QSV_H1(2) QSV_H1(3) QSV_H1(4) QSV_H1(5)
@@ -354,19 +357,34 @@ __device__ __forceinline__ void run_tile(const GenProg &P, const TileArgs &A, fl
             uint32_t rt = 0;
 #pragma unroll
             for (int u = 0; u < T; ++u) rt += ((t >> u) & 1u) * h(R + u);
-            __syncthreads();  // earlier reads of the buffer are complete
-#pragma unroll
-            for (int j = 0; j < N; ++j) lds[wt + j] = make_float2(v.re[j], v.im[j]);
-            __syncthreads();
             uint32_t off[N];
-            off[0] = 0;
+            off[0] = rt;
 #pragma unroll
             for (int j = 1; j < N; ++j) off[j] = off[j & (j - 1)] + h(__builtin_ctz(j));
+            __syncthreads();  // earlier reads of the buffer are complete
+            if constexpr (HALF) {
 #pragma unroll
-            for (int j = 0; j < N; ++j) {
-                const float2 x = lds[rt + off[j]];
-                v.re[j] = x.x;
-                v.im[j] = x.y;
+                for (int j = 0; j < N; ++j) lds[wt + j] = v.re[j];
+                __syncthreads();
+#pragma unroll
+                for (int j = 0; j < N; ++j) v.re[j] = lds[off[j]];
+                __syncthreads();
+#pragma unroll
+                for (int j = 0; j < N; ++j) lds[wt + j] = v.im[j];
+                __syncthreads();
+#pragma unroll
+                for (int j = 0; j < N; ++j) v.im[j] = lds[off[j]];
+            } else {
+                float2 *buf = reinterpret_cast<float2 *>(lds);
+#pragma unroll
+                for (int j = 0; j < N; ++j) buf[wt + j] = make_float2(v.re[j], v.im[j]);
+                __syncthreads();
+#pragma unroll
+                for (int j = 0; j < N; ++j) {
+                    const float2 x = buf[off[j]];
+                    v.re[j] = x.x;
+                    v.im[j] = x.y;
+                }
             }
             break;
         }
@@ -378,6 +396,9 @@ __device__ __forceinline__ void run_tile(const GenProg &P, const TileArgs &A, fl
 #define QSV_T(S) case GEN_T + S: v.template t_gate<S>(__uint_as_float(0x3f3504f3u | op.w[1])); break;
         QSV_T(0) QSV_T(1) QSV_T(2) QSV_T(3) QSV_T(4) QSV_T(5)
 #undef QSV_T
+        case GEN_ZB:
+            extra = (parity(op.w[6] & uint32_t(A.branch)) ^ parity(op.w[7] & uint32_t(A.branch >> 32))) << 31;
+            break;
         case GEN_W: {
             const float2 w = omega(e);
             v.all(w.x, w.y);
@@ -387,7 +408,8 @@ __device__ __forceinline__ void run_tile(const GenProg &P, const TileArgs &A, fl
         case GEN_E: {
             const uint32_t loc = (op.w[0] >> 16) & 0xffu;
             const uint32_t bit = (loc & 0x80u) ? (tile >> (loc & 0x7fu)) & 1u : (t >> loc) & 1u;
-            const uint32_t sg = (parity(op.w[3] & t) ^ parity(op.w[4] & tile) ^ zsign) << 2;
+            const uint32_t sg = (parity(op.w[3] & t) ^ parity(op.w[4] & tile) ^ (extra >> 31)) << 2;
+            extra = 0;
             e += bit * (((op.w[0] >> 8) & 7u) + sg);
             break;
         }
@@ -432,23 +454,23 @@ __device__ __forceinline__ void run_tile(const GenProg &P, const TileArgs &A, fl
     }
 }
 
-template <int R, int T>
+template <int R, int T, bool HALF>
 __global__ void __launch_bounds__(1 << T)
 k_tile(const float2 *src, float2 *amps, const GenProg P, uint64_t branch, uint64_t tile0, int init, float init_val,
        uint64_t basis) {
-    extern __shared__ float2 lds[];
-    run_tile<R, T>(P, TileArgs{src, amps, branch, tile0 + blockIdx.x, basis, init, init_val}, lds);
+    extern __shared__ __attribute__((aligned(16))) float lds[];
+    run_tile<R, T, HALF>(P, TileArgs{src, amps, branch, tile0 + blockIdx.x, basis, init, init_val}, lds);
 }
 
 // One program round of a batch: block b belongs to the segment with the
 // largest start <= b; the segment names the entry (state, branch, programs)
 // and its first tile.  With init_plus an entry's first program starts from
 // |+>^n.
-template <int R, int T>
+template <int R, int T, bool HALF>
 __global__ void __launch_bounds__(1 << T)
 k_tile_batch(const BatchSeg *__restrict__ segs, int nseg, const BatchEntry *__restrict__ ents,
              const GenProg *__restrict__ progs, int round, int init_plus) {
-    extern __shared__ float2 lds[];
+    extern __shared__ __attribute__((aligned(16))) float lds[];
     const uint64_t blk = blockIdx.x;
     int lo = 0, hi = nseg - 1;
     while (lo < hi) {
@@ -458,8 +480,18 @@ k_tile_batch(const BatchSeg *__restrict__ segs, int nseg, const BatchEntry *__re
     const BatchSeg sg = segs[lo];
     const BatchEntry en = ents[sg.entry];
     float2 *a = reinterpret_cast<float2 *>(en.amps);
-    run_tile<R, T>(progs[en.prog0 + round],
+    run_tile<R, T, HALF>(progs[en.prog0 + round],
                    TileArgs{a, a, en.branch, blk - sg.start, 0, (init_plus && round == 0) ? 1 : -1, en.init_val}, lds);
+}
+
+// Exchanges staged in halves when the tiles are more than the CUs hold at once
+// with whole buffers (160 KiB each on 256 CUs): then twice the workgroups on a
+// CU hide each other's waits (23 qubits, tile (5, 8, 5): 137.6 -> 100.4 us,
+// (4, 8, 4): 111.6 -> 101.2); with fewer tiles the extra barriers only cost (22
+// qubits, (4, 8, 4): 71.7 -> 76.6).
+bool stage_halves(int R, int T, uint64_t tiles) {
+    const uint64_t whole = uint64_t(gen_weights(R, T).elems) * sizeof(float2);
+    return tiles > 256 * ((160u << 10) / whole);
 }
 
 template <int R, int T> constexpr size_t tile_lds() { return size_t(gen_weights(R, T).elems) * sizeof(float2); }
@@ -469,33 +501,35 @@ template <class K> hipError_t allow_lds(K kernel, size_t bytes) {
                                int(bytes));
 }
 
-template <int R, int T>
-hipError_t launch_tile_t(const float2 *src, float2 *amps, int n, const GenProg &p, uint64_t branch, int init, uint64_t basis,
-                         hipStream_t s) {
-    static const hipError_t attr = allow_lds(&k_tile<R, T>, tile_lds<R, T>());
+template <int R, int T, bool HALF>
+hipError_t launch_tile_t(const float2 *src, float2 *amps, int n, const GenProg &p, uint64_t branch, int init,
+                         uint64_t basis, hipStream_t s) {
+    constexpr size_t lds = tile_lds<R, T>() / (HALF ? 2 : 1);
+    static const hipError_t attr = allow_lds(&k_tile<R, T, HALF>, lds);
     if (attr != hipSuccess) return attr;
     const uint64_t tiles = 1ull << (n - R - T);
     const uint64_t chunk = 1ull << 30;  // blocks per launch
     const float val = float(1.0 / __builtin_sqrt(double(1ull << n)));
     for (uint64_t t0 = 0; t0 < tiles; t0 += chunk) {
         const uint64_t cnt = (tiles - t0 < chunk) ? tiles - t0 : chunk;
-        hipLaunchKernelGGL((k_tile<R, T>), dim3(unsigned(cnt)), dim3(1 << T), (tile_lds<R, T>()), s, src, amps, p,
-                           branch, t0, init, val, basis);
+        hipLaunchKernelGGL((k_tile<R, T, HALF>), dim3(unsigned(cnt)), dim3(1 << T), lds, s, src, amps, p, branch, t0,
+                           init, val, basis);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }
 
-template <int R, int T>
+template <int R, int T, bool HALF>
 hipError_t launch_tile_batch_t(const BatchSeg *segs, int nseg, const BatchEntry *ents, const GenProg *progs, int round,
                                uint64_t blocks, int init_plus, hipStream_t s) {
-    static const hipError_t attr = allow_lds(&k_tile_batch<R, T>, tile_lds<R, T>());
+    constexpr size_t lds = tile_lds<R, T>() / (HALF ? 2 : 1);
+    static const hipError_t attr = allow_lds(&k_tile_batch<R, T, HALF>, lds);
     if (attr != hipSuccess) return attr;
     if (blocks == 0) return hipSuccess;
     if (blocks > (1ull << 31)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_tile_batch<R, T>), dim3(unsigned(blocks)), dim3(1 << T), (tile_lds<R, T>()), s, segs, nseg,
-                       ents, progs, round, init_plus);
+    hipLaunchKernelGGL((k_tile_batch<R, T, HALF>), dim3(unsigned(blocks)), dim3(1 << T), lds, s, segs, nseg, ents,
+                       progs, round, init_plus);
     return hipGetLastError();
 }
 
@@ -504,7 +538,11 @@ hipError_t launch_tile_batch_t(const BatchSeg *segs, int nseg, const BatchEntry 
 hipError_t launch_tile(const float2 *src, float2 *amps, int n, int R, int T, const GenProg &p, uint64_t branch,
                        int init, uint64_t basis, hipStream_t s) {
     switch (R * 16 + T) {
-#define QSV_SHAPE(RR, TT) case RR * 16 + TT: return launch_tile_t<RR, TT>(src, amps, n, p, branch, init, basis, s);
+#define QSV_SHAPE(RR, TT)                                                                                  \
+    case RR * 16 + TT:                                                                                     \
+        if (stage_halves(RR, TT, 1ull << (n - RR - TT)))                                                       \
+            return launch_tile_t<RR, TT, true>(src, amps, n, p, branch, init, basis, s);                   \
+        return launch_tile_t<RR, TT, false>(src, amps, n, p, branch, init, basis, s);
     QSV_SHAPE(5, 9) QSV_SHAPE(5, 8) QSV_SHAPE(5, 7) QSV_SHAPE(4, 9) QSV_SHAPE(4, 8) QSV_SHAPE(4, 7) QSV_SHAPE(4, 6)
     QSV_SHAPE(3, 6) QSV_SHAPE(3, 4) QSV_SHAPE(2, 3) QSV_SHAPE(6, 8) QSV_SHAPE(6, 7)
 #undef QSV_SHAPE
@@ -515,8 +553,16 @@ hipError_t launch_tile(const float2 *src, float2 *amps, int n, int R, int T, con
 hipError_t launch_tile_batch(int R, int T, const BatchSeg *segs, int nseg, const BatchEntry *ents,
                              const GenProg *progs, int round, uint64_t blocks, int init_plus, hipStream_t s) {
     switch (R * 16 + T) {
-#define QSV_SHAPE(RR, TT) \
-    case RR * 16 + TT: return launch_tile_batch_t<RR, TT>(segs, nseg, ents, progs, round, blocks, init_plus, s);
+#define QSV_SHAPE(RR, TT)                                                                                            \
+    case RR * 16 + TT: {                                                                                             \
+        if (blocks == 0) { /* prepares both forms */                                                                 \
+            const hipError_t e = launch_tile_batch_t<RR, TT, true>(segs, nseg, ents, progs, round, 0, init_plus, s); \
+            if (e != hipSuccess) return e;                                                                           \
+        }                                                                                                            \
+        if (stage_halves(RR, TT, blocks))                                                                            \
+            return launch_tile_batch_t<RR, TT, true>(segs, nseg, ents, progs, round, blocks, init_plus, s);          \
+        return launch_tile_batch_t<RR, TT, false>(segs, nseg, ents, progs, round, blocks, init_plus, s);             \
+    }
     QSV_SHAPE(5, 9) QSV_SHAPE(5, 8) QSV_SHAPE(5, 7) QSV_SHAPE(4, 8) QSV_SHAPE(4, 7)
 #undef QSV_SHAPE
     default: return hipErrorInvalidValue;

@@ -22,21 +22,24 @@ enum GenCode : uint32_t {
     GEN_PROJT = 57,   // projection on a thread or tile-index bit
     GEN_E = 58,       // diagonal of a thread or tile-index bit: adds to the exponent e of w
     GEN_W = 59,       // multiply by w^e, e = 0
+    GEN_ZB = 60,      // sign of the next op from branch bits
     // gate order (see lower_plan)
     GEN_HI = 64,      // + register slot s: (x, y) -> (x - i c y, c y - i x)
     GEN_H2R = 72,     // + pair_index(s1, s2): GEN_H1 on s2, then on s1
     GEN_T = 96,       // + register slot s: y -> e^{+-i pi/4} y, sign bit of the angle in w[1]
 };
 
-// y of GEN_H1/H2/PH is multiplied by w^l (-1)^{parity} before the op, l = 0..7
-// (w = e^{i pi/4}): per operand k = 0, 1 a byte of w[0] (bits 8.. and 16..):
-//   bits 0-2 slot, bit 3 T (l odd), bit 4 I (l & 2), bit 5 neg (l & 4), bit 6 K used
-// w[1 + k]: sign bit of pair p (the registers with bit `slot` set, in order)
-// w[3]: thread partners, operand k in half k;  w[4 + k]: tile-index partners
-// w[6..7]: branch bits whose parity negates (operand 0)
-// GEN_PROJ / GEN_PROJT / GEN_E: bit 8 of w[0]: l is branch bit w[1], else l =
-// w[1]; byte 2 of w[0]: locator (thread bit, or 0x80 | tile-index bit); GEN_E:
-// byte 1 of w[0] = l, partners in w[3], w[4], w[6..7].
+// The second half y of GEN_H1/H2/HI/PH is multiplied by w^l (-1)^{parity} first,
+// l = 0..7 (w = e^{i pi/4}).  Operand k = 0, 1 of an op:
+//   w[0] byte 1 + k: slot in bits 0-2, bit 3 T (l odd: (1 + i) y), bit 4 I
+//                    (l & 2: i y), bit 6: the signs w[1 + k] are used
+//   w[1 + k]: sign bit of pair p (the registers with bit `slot` set, in order)
+//   w[3] half k: thread partners;  w[4 + k]: tile-index partners
+//   w[6 + k]: bits of the FP32 coefficient: 1, or sqrt(1/2) after T; sign l & 4
+// A GEN_ZB in front negates operand 0 by the parity of the branch bits w[6..7].
+// GEN_PROJ / GEN_PROJT: bit 8 of w[0]: l is branch bit w[1], else l = w[1].
+// GEN_PROJT / GEN_E: byte 2 of w[0]: locator (thread bit, or 0x80 | tile-index
+// bit); GEN_E: byte 1 of w[0] = l, partners in w[3] and w[4].
 struct alignas(32) GenOp {
     uint32_t w[8];
 };

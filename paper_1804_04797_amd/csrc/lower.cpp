@@ -23,7 +23,8 @@ namespace qsv {
 
 namespace {
 
-constexpr uint8_t kT = 8, kI = 16, kNeg = 32, kK = 64;
+constexpr uint8_t kT = 8, kI = 16, kK = 64;
+constexpr uint32_t kOne = 0x3f800000u, kSqrtHalf = 0x3f3504f3u, kSign = 0x80000000u;  // FP32 bits
 
 struct Pending {
     int l = 0;        // exponent of w
@@ -160,7 +161,7 @@ struct Lower {
     // operand k of an op on register slot s takes what is pending on its qubit
     void operand(GenOp &g, int k, int s) {
         const Pending &p = pend[occ[s]];
-        uint32_t f = uint32_t(s) | (p.l & 1 ? kT : 0) | (p.l & 2 ? kI : 0) | (p.l & 4 ? kNeg : 0);
+        uint32_t f = uint32_t(s) | (p.l & 1 ? kT : 0) | (p.l & 2 ? kI : 0);
         uint32_t K = 0;
         if (const uint32_t rm = reg_mask(p.cz)) {
             f |= kK;
@@ -173,11 +174,22 @@ struct Lower {
         g.w[1 + k] = K;
         g.w[3] |= thread_mask(p.cz) << (16 * k);
         g.w[4 + k] = tile_mask(p.cz);
-        if (k == 0) {
-            g.w[6] = uint32_t(p.zb);
-            g.w[7] = uint32_t(p.zb >> 32);
-        }
+        g.w[6 + k] = (p.l & 1 ? kSqrtHalf : kOne) | (p.l & 4 ? kSign : 0);
         clear(occ[s]);
+    }
+    // an op on register slot s; branch bits pending on it go in front
+    GenOp &push_on(uint32_t code, int s) {
+        if (n_ops >= kGenOps - 3) split();
+        branch_sign(pend[occ[s]].zb);
+        GenOp &g = push(code);
+        operand(g, 0, s);
+        return g;
+    }
+    void branch_sign(uint64_t zb) {
+        if (!zb) return;
+        GenOp &g = push(GEN_ZB);
+        g.w[6] = uint32_t(zb);
+        g.w[7] = uint32_t(zb >> 32);
     }
     void clear(int q) {
         for (int o = 0; o < 64; ++o)
@@ -191,21 +203,23 @@ struct Lower {
         GenOp *g = open_h1 ? &cur.ops[n_ops - 1] : nullptr;
         const int s1 = g ? int(g->w[0] & 0xff) - GEN_H1 : -1;
         // what the second gate applies must not depend on the first one's slot
-        if (g && s1 != s && !((p.cz >> occ[s1]) & 1) && !p.zb && !(g->w[6] | g->w[7])) {
+        if (g && s1 != s && !((p.cz >> occ[s1]) & 1) && !p.zb) {
             operand(*g, 1, s);
             const bool reversed = s < s1;
             if (reversed) {  // operands in slot order
                 g->w[0] = (g->w[0] & 0xff0000ffu) | ((g->w[0] >> 8) & 0xff00u) | ((g->w[0] & 0xff00u) << 8);
                 std::swap(g->w[1], g->w[2]);
                 std::swap(g->w[4], g->w[5]);
+                std::swap(g->w[6], g->w[7]);
                 g->w[3] = g->w[3] >> 16 | g->w[3] << 16;
             }
             g->w[0] = (g->w[0] & ~0xffu) | uint32_t((reversed && gate_order ? GEN_H2R : GEN_H2) +
                                                     gen_pair_index(std::min(s1, s), std::max(s1, s)));
             open_h1 = false;
         } else {
-            operand(push(uint32_t(GEN_H1 + s)), 0, s);
-            open_h1 = true;
+            const bool plain = !p.zb;
+            push_on(uint32_t(GEN_H1 + s), s);
+            open_h1 = plain;
         }
         pend[occ[s]].l = after;
     }
@@ -213,7 +227,7 @@ struct Lower {
     void imaginary(int s, int before, int after) {
         Pending &p = pend[occ[s]];
         p.l = (p.l + before) & 7;
-        operand(push(uint32_t(GEN_HI + s)), 0, s);
+        push_on(uint32_t(GEN_HI + s), s);
         pend[occ[s]].l = after;
     }
     void phase(uint32_t loc, int k) {
@@ -246,16 +260,16 @@ struct Lower {
     // the rest of the pending diagonal: register slots, then the other qubits
     void closing() {
         for (int s = 0; s < R; ++s)
-            if (pend[occ[s]].any()) operand(push(uint32_t(GEN_PH + s)), 0, s);
+            if (pend[occ[s]].any()) push_on(uint32_t(GEN_PH + s), s);
         for (int q = 0; q < n; ++q) {
             const Pending p = pend[q];
             if (!p.any()) continue;
+            if (n_ops >= kGenOps - 3) split();
+            branch_sign(p.zb);
             GenOp &g = push(GEN_E);
             g.w[0] |= uint32_t(p.l) << 8 | locator(q) << 16;
             g.w[3] = thread_mask(p.cz);
             g.w[4] = tile_mask(p.cz);
-            g.w[6] = uint32_t(p.zb);
-            g.w[7] = uint32_t(p.zb >> 32);
             clear(q);
         }
     }
@@ -344,14 +358,15 @@ void mul_omega(float *z, uint32_t e) {
     const float wr[8] = {1.f, h, 0.f, -h, -1.f, -h, 0.f, h}, wi[8] = {0.f, h, 1.f, h, 0.f, -h, -1.f, -h};
     mul(z, wr[e & 7], wi[e & 7]);
 }
-// sign of operand k in thread t of a tile
-float operand_sign(const uint32_t *w, int k, uint32_t t, uint64_t tile, uint64_t branch) {
-    unsigned sg = parity((w[3] >> (16 * k)) & 0xffff & t) ^ parity(w[4 + k] & tile) ^ ((w[0] >> (13 + 8 * k)) & 1);
-    if (k == 0) sg ^= parity((uint64_t(w[6]) | uint64_t(w[7]) << 32) & branch);
-    return sg ? -1.f : 1.f;
+// coefficient of operand k in thread t of a tile
+float operand_coef(const uint32_t *w, int k, uint32_t t, uint64_t tile, unsigned extra) {
+    const unsigned sg = parity((w[3] >> (16 * k)) & 0xffff & t) ^ parity(w[4 + k] & tile) ^ (k == 0 ? extra : 0u);
+    float c;
+    std::memcpy(&c, &w[6 + k], sizeof c);
+    return sg ? -c : c;
 }
 // The ops that only gate-ordered programs have.
-void emulate_ordered(const uint32_t *w, int R, int T, uint64_t tile, uint64_t branch, float *v) {
+void emulate_ordered(const uint32_t *w, int R, int T, uint64_t tile, unsigned extra, float *v) {
     const int N = 1 << R;
     const uint32_t code = w[0] & 0xff;
     const float h = float(std::sqrt(0.5));
@@ -380,7 +395,7 @@ void emulate_ordered(const uint32_t *w, int R, int T, uint64_t tile, uint64_t br
         signs(1);
         for (int k = 1; k >= 0; --k)
             pairs(int((w[0] >> (8 + 8 * k)) & 7), [&](uint32_t t, float *x, float *y) {
-                const float c = operand_sign(w, k, t, tile, branch);
+                const float c = operand_coef(w, k, t, tile, extra);
                 for (int q = 0; q < 2; ++q) {
                     const float a = x[q] + c * y[q];
                     y[q] = x[q] - c * y[q];
@@ -390,7 +405,7 @@ void emulate_ordered(const uint32_t *w, int R, int T, uint64_t tile, uint64_t br
     } else {
         signs(0);
         pairs(int(code - GEN_HI), [&](uint32_t t, float *x, float *y) {
-            const float c = operand_sign(w, 0, t, tile, branch);
+            const float c = operand_coef(w, 0, t, tile, extra);
             const float xr = x[0] + c * y[1], xi = x[1] - c * y[0], yr = x[1] + c * y[0], yi = c * y[1] - x[0];
             // c y - i x = (c yr + xi, c yi - xr)
             x[0] = xr; x[1] = xi; y[0] = yr; y[1] = yi;
@@ -416,17 +431,20 @@ void emulate_gen(const GenProg &p, int n, int R, int T, uint64_t branch, float *
                 if ((x >> s) & 1) a |= 1ull << gen_phys(phys, s);
             return a;
         };
-        auto par = [](uint64_t x) { return unsigned(__builtin_popcountll(x) & 1); };
         for (uint32_t x = 0; x < (1u << L); ++x)
             std::memcpy(&v[2 * x], amps + 2 * addr(p.ld_phys, x), 2 * sizeof(float));
         std::vector<uint32_t> e(size_t(1) << T, 0u);
+        unsigned extra = 0;  // sign of the next op (GEN_ZB)
         for (uint32_t pc = 0; pc < p.n_ops; ++pc) {
             const uint32_t *w = p.ops[pc].w;
             const uint32_t code = w[0] & 0xff;
-            const uint64_t zb = uint64_t(w[6]) | uint64_t(w[7]) << 32;
             if (code == GEN_END) break;
+            if (code == GEN_ZB) {
+                extra = parity((uint64_t(w[6]) | uint64_t(w[7]) << 32) & branch);
+                continue;
+            }
             if (code >= GEN_HI) {
-                emulate_ordered(w, R, T, tile, branch, v.data());
+                emulate_ordered(w, R, T, tile, extra, v.data());
             } else if (code == GEN_W) {
                 for (uint32_t x = 0; x < (1u << L); ++x) {
                     mul_omega(&v[2 * x], e[x >> R]);
@@ -447,11 +465,8 @@ void emulate_gen(const GenProg &p, int n, int R, int T, uint64_t branch, float *
                         }
                 for (int k = 0; k < nop; ++k)
                     for (uint32_t t = 0; t < (1u << T); ++t) {
-                        const uint32_t f = (w[0] >> (8 + 8 * k)) & 0xff;
-                        const int s = int(f & 7);
-                        unsigned sg = par((w[3] >> (16 * k)) & 0xffff & t) ^ par(w[4 + k] & tile) ^ ((f & kNeg) ? 1 : 0);
-                        if (k == 0) sg ^= par(zb & branch);
-                        const float c = ((f & kT) ? h : 1.f) * (sg ? -1.f : 1.f);
+                        const int s = int((w[0] >> (8 + 8 * k)) & 7);
+                        const float c = operand_coef(w, k, t, tile, extra);
                         for (int j = 0; j < N; ++j) {
                             if ((j >> s) & 1) continue;
                             float *x = &v[2 * (uint32_t(j) | t << R)], *y = &v[2 * (uint32_t(j | 1 << s) | t << R)];
@@ -490,7 +505,7 @@ void emulate_gen(const GenProg &p, int n, int R, int T, uint64_t branch, float *
                 for (uint32_t t = 0; t < (1u << T); ++t) {
                     const uint32_t loc = (w[0] >> 16) & 0xff;
                     const uint32_t bit = (loc & kLocGlobal) ? uint32_t(tile >> (loc & 0x7f)) & 1 : (t >> loc) & 1;
-                    e[t] += bit * (((w[0] >> 8) & 7) + 4 * (par(w[3] & t) ^ par(w[4] & tile) ^ par(zb & branch)));
+                    e[t] += bit * (((w[0] >> 8) & 7) + 4 * (parity(w[3] & t) ^ parity(w[4] & tile) ^ extra));
                 }
             } else {  // projections
                 const uint32_t l = (w[0] >> 8) & 1 ? uint32_t(branch >> w[1]) & 1 : w[1], loc = (w[0] >> 16) & 0xff;
@@ -501,6 +516,7 @@ void emulate_gen(const GenProg &p, int n, int R, int T, uint64_t branch, float *
                     if (bit != l) v[2 * x] = v[2 * x + 1] = 0.f;
                 }
             }
+            extra = 0;
         }
         const float wr[8] = {1.f, h, 0.f, -h, -1.f, -h, 0.f, h}, wi[8] = {0.f, h, 1.f, h, 0.f, -h, -1.f, -h};
         for (uint32_t x = 0; x < (1u << L); ++x) {
