@@ -512,13 +512,10 @@ qsv_status sv_branch_combine_full(const void *a_states, const void *b_states, si
  * generic pass kernel, one launch per tile shape and pass round.  States of
  * 2^21 amplitudes or more run compiled kernels of their own plan on the tile
  * shape tuned for their class (sv_tune / sv_tune_set); in the captured graph
- * each such plan's chain of passes is a branch of its own, so independent
- * states run side by side (the batch makes four side streams for the
- * capture when it has two or more such plans).  A persistent form
- * (one launch per tile shape whose workgroups take work items (pass round,
- * entry, tile) in order from a device counter, per-entry counters of
- * completed tiles ordering each entry's passes) is switched off in this
- * version: QSV_BATCH_PERSISTENT=1 makes sv_batch_create return
+ * the passes of each such plan and the rounds of each tile shape are a branch
+ * of their own, so independent states run side by side (the batch makes four
+ * side streams for the capture when it has two or more branches).  There is
+ * no persistent form: QSV_BATCH_PERSISTENT=1 makes sv_batch_create return
  * QSV_EUNSUPPORTED.
  *
  * sv_batch_create: count entries; entry i runs circuit circs[i] with branch
@@ -536,12 +533,9 @@ qsv_status sv_branch_combine_full(const void *a_states, const void *b_states, si
  * calls with the same pointers replay it.  Asynchronous on stream; the
  * bitstrings are not range-checked (the replayed graph cannot wait for a
  * check): an entry's bitstring >= 2^n_i gives NaN in its table slot.
- * sv_batch_status: synchronises stream and reports QSV_EINTERNAL if a wait of
- * a persistent launch gave up since the last status call (its bounded spin
- * ran out, or sv_batch_abort was called): the results of that run are then
- * unspecified.  Clears the abort request.
- * sv_batch_abort: asks the waits of the batch's launches in flight to give up
- * (host only; a pinned flag they poll), so every launch drains promptly.
+ * sv_batch_status: synchronises stream and reports an error of the work on it.
+ * sv_batch_abort: no launch of a batch waits on another one, so there is
+ * nothing to give up; QSV_OK.
  */
 qsv_status sv_batch_create(const qsv_circuit *const *circs, const uint64_t *branch_ids,
                            size_t count, const qsv_fuse_opts *opts, qsv_batch **out);

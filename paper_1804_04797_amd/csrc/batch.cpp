@@ -64,8 +64,8 @@ struct qsv_batch {
     // captured graph and the arguments it was captured for
     hipGraphExec_t exec = nullptr;
     hipStream_t cap = nullptr;
-    // side streams of the capture: the compiled plans' launches become
-    // parallel branches of the graph (fork and join events)
+    // side streams of the capture: the chains of launches become parallel
+    // branches of the graph (fork and join events)
     std::vector<hipStream_t> lanes;
     std::vector<hipEvent_t> lane_done;
     hipEvent_t fork = nullptr;
@@ -367,7 +367,7 @@ qsv_status sv_batch_create(const qsv_circuit *const *circs, const uint64_t *bran
     hipError_t e = hipSuccess;
     static const int kShapes[][2] = {{5, 9}, {5, 8}, {4, 8}, {5, 7}, {4, 7}};
     for (auto &sh : kShapes)
-        if (e == hipSuccess) e = launch_tile_batch(sh[0], sh[1], nullptr, 0, nullptr, nullptr, 0, 0, 0, nullptr);
+        if (e == hipSuccess) e = launch_tile_batch(sh[0], sh[1], nullptr, 0, nullptr, nullptr, 0, 0, 0, true, nullptr);
     if (e != hipSuccess) return fail(QSV_EHIP, std::string("sv_batch_create: ") + hipGetErrorString(e));
     e = hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking);
     if (e != hipSuccess) return fail(QSV_EHIP, "sv_batch_create: capture stream");
@@ -433,10 +433,29 @@ qsv_status sv_batch_run(qsv_batch *b, void *const *amps_dev, int init_plus,
             for (qsv_status r : res)
                 if (r != QSV_OK) return fail(r, "sv_batch_run: compiling pass kernels failed");
         }
+        // chains of launches: the passes of a compiled plan, the rounds of a
+        // tile shape; compiled ones first, then by work
+        struct Chain {
+            double work;
+            size_t plan, shape;  // shape == ~0: compiled plan
+        };
+        std::vector<Chain> chains;
+        for (size_t p : jp)
+            chains.push_back({double(b->group[p].size()) * std::ldexp(double(b->plans[p]->passes.size()), b->plans[p]->n),
+                              p, ~size_t(0)});
+        for (size_t k = 0; k < b->shapes.size(); ++k) {
+            double blocks = 0;
+            for (uint64_t x : b->shapes[k].round_blocks) blocks += double(x);
+            // an interpreted pass costs about twice a compiled one
+            chains.push_back({2.0 * std::ldexp(blocks, b->shapes[k].R + b->shapes[k].T), 0, k});
+        }
+        std::stable_sort(chains.begin(), chains.end(), [](const Chain &x, const Chain &y) {
+            const bool xs = x.shape != ~size_t(0), ys = y.shape != ~size_t(0);
+            return xs != ys ? ys : x.work > y.work;
+        });
         // the side streams and their events (below), made before the first
-        // capture that has two compiled chains to run side by side
-        if (std::count_if(b->plan_jit.begin(), b->plan_jit.end(), [](char j) { return j != 0; }) > 1 &&
-            b->lanes.empty()) {
+        // capture that has two chains to run side by side
+        if (chains.size() > 1 && b->lanes.empty()) {
             e = hipEventCreateWithFlags(&b->fork, hipEventDisableTiming);
             for (int k = 0; k < kLanes && e == hipSuccess; ++k) {
                 hipStream_t ls = nullptr;
@@ -454,40 +473,41 @@ qsv_status sv_batch_run(qsv_batch *b, void *const *amps_dev, int init_plus,
         e = hipStreamBeginCapture(b->cap, hipStreamCaptureModeThreadLocal);
         if (e != hipSuccess) return hipfail(e, "sv_batch_run: begin capture");
         hipError_t le = hipSuccess;
-        // Each compiled plan's passes form a chain of their own: the chains
-        // go to the side streams (largest work first, each to the least
-        // loaded stream), so the graph holds them as parallel branches and
-        // small states do not leave the device idle one after another; the
-        // generic-kernel rounds stay on the capture stream, alongside.
-        std::vector<size_t> jplans;
-        for (size_t p = 0; p < b->plans.size(); ++p)
-            if (b->plan_jit[p]) jplans.push_back(p);
-        auto work = [&](size_t p) {
-            return double(b->group[p].size()) * std::ldexp(double(b->plans[p]->passes.size()), b->plans[p]->n);
-        };
-        std::stable_sort(jplans.begin(), jplans.end(), [&](size_t x, size_t y) { return work(x) > work(y); });
+        // The chains go to the capture stream and the side streams, each to the
+        // least loaded one, so the graph holds them as parallel branches and
+        // small states do not leave the device idle one after another (40
+        // circuits of 12..16 qubits, four tile shapes: 173 -> 79 us).
         size_t joined = 0;  // side streams that joined the capture
-        if (le == hipSuccess && jplans.size() > 1 && !b->lanes.empty()) {
+        if (chains.size() > 1 && !b->lanes.empty()) {
             le = hipEventRecord(b->fork, b->cap);
             while (le == hipSuccess && joined < b->lanes.size()) {
                 le = hipStreamWaitEvent(b->lanes[joined], b->fork, 0);
                 if (le == hipSuccess) ++joined;
             }
         }
-        std::vector<double> load(std::max<size_t>(joined, 1), 0.0);
-        for (size_t p : jplans) {
+        std::vector<double> load(joined + 1, 0.0);  // the last one: the capture stream
+        for (const Chain &ch : chains) {
             if (le != hipSuccess) break;
-            const size_t k = size_t(std::min_element(load.begin(), load.end()) - load.begin());
-            load[k] += work(p);
-            if (jit_launch_batched(*b->plans[p], variant, b->d_group_ents[p], unsigned(b->group[p].size()),
-                                   joined ? b->lanes[k] : b->cap) != QSV_OK)
-                le = hipErrorLaunchFailure;
-        }
-        for (const BatchShape &bs : b->shapes) {
-            if (le != hipSuccess) break;
+            // beside compiled chains the capture stream is kept for the tile
+            // shapes, whose launches are the many short ones (32 circuits of
+            // 14..24 qubits: 835 us; spread over all streams 872)
+            size_t k = size_t(std::min_element(load.begin(), load.end()) - load.begin());
+            if (!jp.empty() && joined)
+                k = ch.shape != ~size_t(0)
+                        ? joined
+                        : size_t(std::min_element(load.begin(), load.end() - 1) - load.begin());
+            const hipStream_t ls = k < joined ? b->lanes[k] : b->cap;
+            load[k] += ch.work;
+            if (ch.shape == ~size_t(0)) {
+                if (jit_launch_batched(*b->plans[ch.plan], variant, b->d_group_ents[ch.plan],
+                                       unsigned(b->group[ch.plan].size()), ls) != QSV_OK)
+                    le = hipErrorLaunchFailure;
+                continue;
+            }
+            const BatchShape &bs = b->shapes[ch.shape];
             for (size_t r = 0; r < bs.round_blocks.size() && le == hipSuccess; ++r)
                 le = launch_tile_batch(bs.R, bs.T, bs.d_segs + bs.round_seg_off[r], bs.round_nseg[r], b->d_ents,
-                                       b->d_progs, int(r), bs.round_blocks[r], init_plus ? 1 : 0, b->cap);
+                                       b->d_progs, int(r), bs.round_blocks[r], init_plus ? 1 : 0, jp.empty(), ls);
         }
         // join every side stream back (also after an error: the capture
         // must end with all of them joined)

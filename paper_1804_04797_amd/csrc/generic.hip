@@ -488,7 +488,9 @@ k_tile_batch(const BatchSeg *__restrict__ segs, int nseg, const BatchEntry *__re
 // with whole buffers (160 KiB each on 256 CUs): then twice the workgroups on a
 // CU hide each other's waits (23 qubits, tile (5, 8, 5): 137.6 -> 100.4 us,
 // (4, 8, 4): 111.6 -> 101.2); with fewer tiles the extra barriers only cost (22
-// qubits, (4, 8, 4): 71.7 -> 76.6).
+// qubits, (4, 8, 4): 71.7 -> 76.6).  Beside compiled passes, which fill the
+// device anyway, a batch's rounds stay whole (32 circuits of 14..24 qubits: 835
+// us, 852 in halves; 40 generic ones of 16..20 qubits: 220, 199 in halves).
 bool stage_halves(int R, int T, uint64_t tiles) {
     const uint64_t whole = uint64_t(gen_weights(R, T).elems) * sizeof(float2);
     return tiles > 256 * ((160u << 10) / whole);
@@ -551,7 +553,8 @@ hipError_t launch_tile(const float2 *src, float2 *amps, int n, int R, int T, con
 }
 
 hipError_t launch_tile_batch(int R, int T, const BatchSeg *segs, int nseg, const BatchEntry *ents,
-                             const GenProg *progs, int round, uint64_t blocks, int init_plus, hipStream_t s) {
+                             const GenProg *progs, int round, uint64_t blocks, int init_plus, bool alone,
+                             hipStream_t s) {
     switch (R * 16 + T) {
 #define QSV_SHAPE(RR, TT)                                                                                            \
     case RR * 16 + TT: {                                                                                             \
@@ -559,7 +562,7 @@ hipError_t launch_tile_batch(int R, int T, const BatchSeg *segs, int nseg, const
             const hipError_t e = launch_tile_batch_t<RR, TT, true>(segs, nseg, ents, progs, round, 0, init_plus, s); \
             if (e != hipSuccess) return e;                                                                           \
         }                                                                                                            \
-        if (stage_halves(RR, TT, blocks))                                                                            \
+        if (alone && stage_halves(RR, TT, blocks))                                                                   \
             return launch_tile_batch_t<RR, TT, true>(segs, nseg, ents, progs, round, blocks, init_plus, s);          \
         return launch_tile_batch_t<RR, TT, false>(segs, nseg, ents, progs, round, blocks, init_plus, s);             \
     }

@@ -20,9 +20,11 @@ bool compiled_shape_supported(int R, int T);
 hipError_t launch_tile(const float2 *src, float2 *amps, int n, int R, int T, const GenProg &p, uint64_t branch,
                        int init, uint64_t basis, hipStream_t s);
 // One program round of a batch: `blocks` tiles of the entries in segs.
-// blocks == 0 only prepares the kernel (outside a capture).
+// blocks == 0 only prepares the kernel (outside a capture).  alone: no compiled
+// passes run beside it.
 hipError_t launch_tile_batch(int R, int T, const BatchSeg *segs, int nseg, const BatchEntry *ents,
-                             const GenProg *progs, int round, uint64_t blocks, int init_plus, hipStream_t s);
+                             const GenProg *progs, int round, uint64_t blocks, int init_plus, bool alone,
+                             hipStream_t s);
 hipError_t launch_gather_batch(const BatchEntry *ents, uint64_t count, const uint64_t *xs,
                                uint64_t m, float2 *out, hipStream_t s);
 hipError_t launch_dense(float2 *amps, int n, int k, const int *qubits, const float *mat_t,
