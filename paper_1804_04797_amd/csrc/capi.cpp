@@ -340,15 +340,17 @@ void gate_matrix_f32(uint8_t kind, float m[8]) {
 }  // namespace
 
 // Every lowered program of the plan (at least one) on amps; the first one
-// reads src, or starts from the initial state of kind init (>= 0).
+// reads src, or starts from the initial state of kind init (>= 0); the last one
+// writes each tile's sum of |amp|^2 to norm unless that is null.
 static qsv_status run_generic(Plan &plan, bool gate_order, const void *src, void *amps, uint64_t branch, int init,
-                              uint64_t basis, hipStream_t s, const char *who) {
+                              uint64_t basis, double *norm, hipStream_t s, const char *who) {
     std::shared_ptr<const std::vector<GenProg>> progs;
     qsv_status st = generic_programs(plan, gate_order, progs);
     if (st != QSV_OK) return st;
     const float2 *in = static_cast<const float2 *>(src);
     for (const GenProg &p : *progs) {
-        hipError_t e = launch_tile(in, static_cast<float2 *>(amps), plan.n, plan.R, plan.T, p, branch, init, basis, s);
+        hipError_t e = launch_tile(in, static_cast<float2 *>(amps), plan.n, plan.R, plan.T, p, branch, init, basis,
+                                   &p == &progs->back() ? norm : nullptr, s);
         if (e != hipSuccess) return fail(QSV_EHIP, std::string(who) + ": " + hipGetErrorString(e));
         in = static_cast<const float2 *>(amps);
         init = -1;
@@ -548,7 +550,7 @@ qsv_status sv_apply_fused(void *amps, const qsv_circuit *c, uint64_t branch, int
     if (!fused_shape_supported(sh.R, sh.T))
         return fail(QSV_EUNSUPPORTED, "sv_apply_fused: this tile shape runs compiled passes only (jit >= 1)");
     if ((st = get_plan(c, layer_begin, layer_end, sh, plan)) != QSV_OK) return st;
-    return run_generic(*plan, false, amps, amps, branch, -1, 0, s, "sv_apply_fused");
+    return run_generic(*plan, false, amps, amps, branch, -1, 0, nullptr, s, "sv_apply_fused");
 }
 
 qsv_status sv_apply_fused_from(const void *src, void *dst, const qsv_circuit *c, uint64_t branch,
@@ -598,7 +600,7 @@ qsv_status sv_apply_fused_from(const void *src, void *dst, const qsv_circuit *c,
     if (fused && fused_shape_supported(sh.R, sh.T)) {  // generic kernel: its first program reads src
         std::shared_ptr<Plan> plan;
         if ((st = get_plan(c, layer_begin, layer_end, sh, plan)) != QSV_OK) return st;
-        if (!plan->passes.empty()) return run_generic(*plan, false, src, dst, branch, -1, 0, s, "sv_apply_fused_from");
+        if (!plan->passes.empty()) return run_generic(*plan, false, src, dst, branch, -1, 0, nullptr, s, "sv_apply_fused_from");
     }
     // per-gate path or no gates: copy, then sweep dst in place
     hipError_t e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToDevice, s);
@@ -1085,6 +1087,8 @@ qsv_status sv_simulate(void *amps, const qsv_circuit *c, uint64_t branch, int in
     const int jm = fused ? jit_mode(c, opts) : 0;
     void *scratch = nullptr;
     double *part = nullptr;
+    uint64_t partials = 0;  // partial sums of the norm to add up
+    bool normed = false;    // the sweep itself left the norm or its partials
     if (jm) {
         const uint64_t tiles = 1ull << (c->n - sh.R - sh.T);
         const size_t need = norm_out_dev ? tiles * sizeof(double) : 0;
@@ -1104,13 +1108,11 @@ qsv_status sv_simulate(void *amps, const qsv_circuit *c, uint64_t branch, int in
         }
         const uint64_t tiles = 1ull << (c->n - sh.R - sh.T);
         if ((st = jit_launch(*plan, variant, amps, scratch, branch, basis, part, s)) != QSV_OK) return st;
-        if (norm_out_dev) {
-            hipError_t e = launch_sum_partials(part, tiles, norm_out_dev, s);
-            if (e != hipSuccess) return hip_fail(e, "sv_simulate");
-        }
+        partials = norm_out_dev ? tiles : 0;
     } else {
         // generic kernel or per-gate path: init, sweep in place, then the
-        // norm's own reduction with its partial sums in the workspace
+        // norm's partial sums in the workspace, from the last program or, where
+        // the tiles are more than the reduction's own blocks, from that
         const size_t need = norm_out_dev ? norm_partial_count(c->n) * sizeof(double) : 0;
         if (need && (!ws.p || ws.bytes < need))
             return fail(QSV_EINVAL, "sv_simulate: the FP64 norm needs a workspace of sv_workspace_bytes bytes");
@@ -1119,25 +1121,36 @@ qsv_status sv_simulate(void *amps, const qsv_circuit *c, uint64_t branch, int in
             // the first program generates the initial state
             if (!fused_shape_supported(sh.R, sh.T))
                 return fail(QSV_EUNSUPPORTED, "sv_simulate: this tile shape runs compiled passes only (jit >= 1)");
-            if ((st = run_generic(*plan, true, amps, amps, branch, init_kind, basis, s, "sv_simulate")) != QSV_OK)
+            const uint64_t tiles = 1ull << (c->n - sh.R - sh.T);
+            double *norm = nullptr;
+            if (norm_out_dev && tiles == 1) {
+                norm = norm_out_dev;
+            } else if (norm_out_dev && tiles <= norm_partial_count(c->n)) {
+                norm = part = reinterpret_cast<double *>(ws.p);
+                partials = tiles;
+            }
+            normed = norm != nullptr;
+            if ((st = run_generic(*plan, true, amps, amps, branch, init_kind, basis, norm, s, "sv_simulate")) != QSV_OK)
                 return st;
         } else {
             e = launch_init(static_cast<float2 *>(amps), c->n, init_kind, basis, s);
             if (e != hipSuccess) return hip_fail(e, "sv_simulate");
             if (!fused && (st = sv_apply_plain(amps, c, branch, layer_begin, layer_end, stream)) != QSV_OK) return st;
         }
-        if (norm_out_dev) {
+        if (norm_out_dev && !normed) {
             e = launch_norm(static_cast<const float2 *>(amps), c->n, norm_out_dev, reinterpret_cast<double *>(ws.p),
                             s);
             if (e != hipSuccess) return hip_fail(e, "sv_simulate: norm");
         }
     }
-    if (m) {
-        hipError_t e = launch_gather(static_cast<const float2 *>(amps), c->n, bitstrings_dev, m,
-                                     amps_out_dev, out_c128 ? 1 : 0, s);
-        if (e != hipSuccess) return hip_fail(e, "sv_simulate");
-    }
-    return QSV_OK;
+    hipError_t e = hipSuccess;
+    if (partials)
+        e = launch_finish(part, partials, norm_out_dev, static_cast<const float2 *>(amps), c->n, bitstrings_dev, m,
+                          amps_out_dev, out_c128 ? 1 : 0, s);
+    else if (m)
+        e = launch_gather(static_cast<const float2 *>(amps), c->n, bitstrings_dev, m, amps_out_dev, out_c128 ? 1 : 0,
+                          s);
+    return e == hipSuccess ? QSV_OK : hip_fail(e, "sv_simulate");
 }
 
 qsv_status sv_simulate_dot(void *amps, const qsv_circuit *c, uint64_t branch, int init_kind,

@@ -240,6 +240,7 @@ struct TileArgs {
     uint64_t branch, tile, basis;
     int init;  // -1: load the tile; 0 / 2: |basis>; 1: every amplitude init_val
     float init_val;
+    double *norm;  // null, or the tiles' sums of |amp|^2
 };
 
 // e^{i pi k / 4}
@@ -452,14 +453,33 @@ __device__ __forceinline__ void run_tile(const GenProg &P, const TileArgs &A, fl
         const v4f w = {v.re[j], v.im[j], v.re[j + 1], v.im[j + 1]};
         *reinterpret_cast<v4f *>(dst + reg_offset(P.st_phys, j)) = w;
     }
+    if (A.norm) {
+        // FP64 products of FP32 values are exact; fixed thread, lane, wave order.
+        // Saves the norm's own read of the state and two launches (with the
+        // gather in k_finish; 23 qubits: 164.5 -> 153.1 us, 20: 73.3 -> 69.9)
+        double acc = 0.0;
+#pragma unroll
+        for (int j = 0; j < N; ++j) acc += double(v.re[j]) * double(v.re[j]) + double(v.im[j]) * double(v.im[j]);
+        constexpr int kLanes = T < 6 ? 1 << T : 64;
+        for (int h = kLanes / 2; h > 0; h >>= 1) acc += __shfl_down(acc, h, kLanes);
+        if constexpr (T > 6) {
+            double *s = reinterpret_cast<double *>(lds);
+            __syncthreads();  // the last exchange has been read
+            if ((t & 63u) == 0) s[t >> 6] = acc;
+            __syncthreads();
+            if (t == 0)
+                for (int k = 1; k < (1 << (T - 6)); ++k) acc += s[k];
+        }
+        if (t == 0) A.norm[tile] = acc;
+    }
 }
 
 template <int R, int T, bool HALF>
 __global__ void __launch_bounds__(1 << T)
 k_tile(const float2 *src, float2 *amps, const GenProg P, uint64_t branch, uint64_t tile0, int init, float init_val,
-       uint64_t basis) {
+       uint64_t basis, double *norm) {
     extern __shared__ __attribute__((aligned(16))) float lds[];
-    run_tile<R, T, HALF>(P, TileArgs{src, amps, branch, tile0 + blockIdx.x, basis, init, init_val}, lds);
+    run_tile<R, T, HALF>(P, TileArgs{src, amps, branch, tile0 + blockIdx.x, basis, init, init_val, norm}, lds);
 }
 
 // One program round of a batch: block b belongs to the segment with the
@@ -480,8 +500,9 @@ k_tile_batch(const BatchSeg *__restrict__ segs, int nseg, const BatchEntry *__re
     const BatchSeg sg = segs[lo];
     const BatchEntry en = ents[sg.entry];
     float2 *a = reinterpret_cast<float2 *>(en.amps);
-    run_tile<R, T, HALF>(progs[en.prog0 + round],
-                   TileArgs{a, a, en.branch, blk - sg.start, 0, (init_plus && round == 0) ? 1 : -1, en.init_val}, lds);
+    run_tile<R, T, HALF>(
+        progs[en.prog0 + round],
+        TileArgs{a, a, en.branch, blk - sg.start, 0, (init_plus && round == 0) ? 1 : -1, en.init_val, nullptr}, lds);
 }
 
 // Exchanges staged in halves when the tiles are more than the CUs hold at once
@@ -505,7 +526,7 @@ template <class K> hipError_t allow_lds(K kernel, size_t bytes) {
 
 template <int R, int T, bool HALF>
 hipError_t launch_tile_t(const float2 *src, float2 *amps, int n, const GenProg &p, uint64_t branch, int init,
-                         uint64_t basis, hipStream_t s) {
+                         uint64_t basis, double *norm, hipStream_t s) {
     constexpr size_t lds = tile_lds<R, T>() / (HALF ? 2 : 1);
     static const hipError_t attr = allow_lds(&k_tile<R, T, HALF>, lds);
     if (attr != hipSuccess) return attr;
@@ -515,7 +536,7 @@ hipError_t launch_tile_t(const float2 *src, float2 *amps, int n, const GenProg &
     for (uint64_t t0 = 0; t0 < tiles; t0 += chunk) {
         const uint64_t cnt = (tiles - t0 < chunk) ? tiles - t0 : chunk;
         hipLaunchKernelGGL((k_tile<R, T, HALF>), dim3(unsigned(cnt)), dim3(1 << T), lds, s, src, amps, p, branch, t0,
-                           init, val, basis);
+                           init, val, basis, norm);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -538,13 +559,13 @@ hipError_t launch_tile_batch_t(const BatchSeg *segs, int nseg, const BatchEntry 
 }  // namespace
 
 hipError_t launch_tile(const float2 *src, float2 *amps, int n, int R, int T, const GenProg &p, uint64_t branch,
-                       int init, uint64_t basis, hipStream_t s) {
+                       int init, uint64_t basis, double *norm, hipStream_t s) {
     switch (R * 16 + T) {
 #define QSV_SHAPE(RR, TT)                                                                                  \
     case RR * 16 + TT:                                                                                     \
         if (stage_halves(RR, TT, 1ull << (n - RR - TT)))                                                       \
-            return launch_tile_t<RR, TT, true>(src, amps, n, p, branch, init, basis, s);                   \
-        return launch_tile_t<RR, TT, false>(src, amps, n, p, branch, init, basis, s);
+            return launch_tile_t<RR, TT, true>(src, amps, n, p, branch, init, basis, norm, s);                 \
+        return launch_tile_t<RR, TT, false>(src, amps, n, p, branch, init, basis, norm, s);
     QSV_SHAPE(5, 9) QSV_SHAPE(5, 8) QSV_SHAPE(5, 7) QSV_SHAPE(4, 9) QSV_SHAPE(4, 8) QSV_SHAPE(4, 7) QSV_SHAPE(4, 6)
     QSV_SHAPE(3, 6) QSV_SHAPE(3, 4) QSV_SHAPE(2, 3) QSV_SHAPE(6, 8) QSV_SHAPE(6, 7)
 #undef QSV_SHAPE

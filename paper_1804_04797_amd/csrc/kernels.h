@@ -16,9 +16,10 @@ bool fused_shape_supported(int R, int T);
 bool compiled_shape_supported(int R, int T);
 // One lowered program over every tile of a state (generic.hip): reads src (amps,
 // or another state, which stays as it is) and writes amps.  init >= 0: the
-// tiles start from the initial state of that kind (sv_init) instead.
+// tiles start from the initial state of that kind (sv_init) instead.  norm: null,
+// or tile k's sum of |amp|^2 goes to norm[k].
 hipError_t launch_tile(const float2 *src, float2 *amps, int n, int R, int T, const GenProg &p, uint64_t branch,
-                       int init, uint64_t basis, hipStream_t s);
+                       int init, uint64_t basis, double *norm, hipStream_t s);
 // One program round of a batch: `blocks` tiles of the entries in segs.
 // blocks == 0 only prepares the kernel (outside a capture).  alone: no compiled
 // passes run beside it.
@@ -65,6 +66,9 @@ struct CombineArgs {
 hipError_t launch_combine_gemm(const float2 *A, const float2 *B, uint64_t nbr, const CombineArgs &P,
                                void *out, bool fp64, bool out_c128, hipStream_t s);
 hipError_t launch_sum_partials(const double *part, uint64_t count, double *out, hipStream_t s);
+// norm = sum of the partials, and launch_gather, in one launch
+hipError_t launch_finish(const double *part, uint64_t count, double *norm, const float2 *amps, int n,
+                         const uint64_t *xs, uint64_t m, void *out, int c128, hipStream_t s);
 // dst = src, bytes a multiple of 16, both 16-byte aligned
 hipError_t launch_stream_copy(const void *src, void *dst, uint64_t bytes, hipStream_t s);
 hipError_t launch_branch_combine(const float2 *A, const float2 *B, uint64_t nb, uint64_t m,

@@ -458,10 +458,9 @@ k_init_small(float2 *__restrict__ a, uint64_t dim, float val, int kind, uint64_t
     else a[i] = f2(i == basis ? 1.f : 0.f, 0.f);
 }
 
-__global__ void __launch_bounds__(256)
-k_gather(const float2 *__restrict__ a, uint64_t dim, const uint64_t *__restrict__ xs, uint64_t m,
-         void *__restrict__ out, int c128) {
-    const uint64_t k = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+// out[k] = amplitude of bitstring xs[k] (NaN beyond the state)
+__device__ __forceinline__ void gather_one(const float2 *a, uint64_t dim, const uint64_t *xs, uint64_t m, void *out,
+                                           int c128, uint64_t k) {
     if (k >= m) return;
     const uint64_t x = xs[k];
     float2 v;
@@ -469,6 +468,12 @@ k_gather(const float2 *__restrict__ a, uint64_t dim, const uint64_t *__restrict_
     else v = f2(__builtin_nanf(""), __builtin_nanf(""));
     if (c128) reinterpret_cast<double2 *>(out)[k] = make_double2(double(v.x), double(v.y));
     else reinterpret_cast<float2 *>(out)[k] = v;
+}
+
+__global__ void __launch_bounds__(256)
+k_gather(const float2 *__restrict__ a, uint64_t dim, const uint64_t *__restrict__ xs, uint64_t m,
+         void *__restrict__ out, int c128) {
+    gather_one(a, dim, xs, m, out, c128, uint64_t(blockIdx.x) * blockDim.x + threadIdx.x);
 }
 
 // Range check of device bitstrings: raises *flag (mapped host memory) when
@@ -523,11 +528,9 @@ k_norm_partial(const v4f *__restrict__ a, uint64_t quads_per_block, double *__re
 
 // Sum of count partials by one block of 1024 threads: each thread keeps
 // eight independent accumulators over a fixed strided subset, then a fixed
-// tree over the threads.  Block b sums the b-th run of count partials.
-__global__ void __launch_bounds__(1024)
-k_sum_partials(const double *__restrict__ part, uint64_t count, double *__restrict__ out) {
+// tree over the threads.
+__device__ __forceinline__ void sum_partials(const double *part, uint64_t count, double *out) {
     __shared__ double s[1024];
-    part += blockIdx.x * count;
     double acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     uint64_t i = threadIdx.x;
     for (; i + 7 * 1024 < count; i += 8 * 1024) {
@@ -541,7 +544,22 @@ k_sum_partials(const double *__restrict__ part, uint64_t count, double *__restri
         if (int(threadIdx.x) < h) s[threadIdx.x] += s[threadIdx.x + h];
         __syncthreads();
     }
-    if (threadIdx.x == 0) out[blockIdx.x] = s[0];
+    if (threadIdx.x == 0) *out = s[0];
+}
+
+// Block b sums the b-th run of count partials.
+__global__ void __launch_bounds__(1024)
+k_sum_partials(const double *__restrict__ part, uint64_t count, double *__restrict__ out) {
+    sum_partials(part + blockIdx.x * count, count, out + blockIdx.x);
+}
+
+// What ends a simulation, in one launch: block 0 sums the norm's partials, the
+// others gather the amplitudes.
+__global__ void __launch_bounds__(1024)
+k_finish(const double *__restrict__ part, uint64_t count, double *__restrict__ norm, const float2 *__restrict__ a,
+         uint64_t dim, const uint64_t *__restrict__ xs, uint64_t m, void *__restrict__ out, int c128) {
+    if (blockIdx.x == 0) sum_partials(part, count, norm);
+    else gather_one(a, dim, xs, m, out, c128, uint64_t(blockIdx.x - 1) * 1024 + threadIdx.x);
 }
 
 // <a|b> = sum conj(a_i) b_i with FP64 products of the FP32 inputs (exact),
@@ -869,6 +887,17 @@ hipError_t launch_stream_copy(const void *src, void *dst, uint64_t bytes, hipStr
 
 hipError_t launch_sum_partials(const double *part, uint64_t count, double *out, hipStream_t s) {
     hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(1024), 0, s, part, count, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_finish(const double *part, uint64_t count, double *norm, const float2 *amps, int n,
+                         const uint64_t *xs, uint64_t m, void *out, int c128, hipStream_t s) {
+    if (m > (1ull << 30)) {
+        const hipError_t e = launch_sum_partials(part, count, norm, s);
+        return e == hipSuccess ? launch_gather(amps, n, xs, m, out, c128, s) : e;
+    }
+    hipLaunchKernelGGL(k_finish, dim3(1 + unsigned((m + 1023) / 1024)), dim3(1024), 0, s, part, count, norm, amps,
+                       1ull << n, xs, m, out, c128);
     return hipGetLastError();
 }
 

@@ -120,3 +120,29 @@ def test_default_shapes_on_device(n, depth):
     qsv.sv_apply_fused(b, c)
     for x in (a, b):
         _check(x.cpu().numpy().astype(np.complex128), ref, gates)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,shape,m", [
+    (7, (3, 4, 3), 1), (9, (3, 4, 3), 5), (11, (4, 7, 4), 100), (12, (4, 7, 4), 0), (13, (4, 8, 4), 1),
+    (14, (4, 6, 4), 7), (14, (5, 8, 5), 1024), (16, (4, 7, 4), 1025), (15, (5, 9, 4), 3), (17, (4, 8, 4), 64)])
+def test_norm_from_the_last_program(n, shape, m):
+    """One tile, tiles up to the reduction's own block count (n >= 14) and more
+    of them.  A sum of nonnegative FP64 terms with at most 2^8 additions on any
+    path to the result: relative error <= 2^8 * 2^-53 each."""
+    import torch
+    c = _explicit(n, 120, 90 + n)
+    o = {"reg_qubits": shape[0], "thread_qubits": shape[1], "low_qubits": shape[2], "jit": -1}
+    a = torch.empty(1 << n, dtype=torch.complex64, device="cuda")
+    norm = torch.full((1,), -1.0, dtype=torch.float64, device="cuda")
+    rng = np.random.default_rng(n)
+    bits = torch.from_numpy(rng.integers(0, 1 << n, max(m, 1)).astype(np.int64)).cuda()
+    out = torch.zeros(max(m, 1), dtype=torch.complex64, device="cuda")
+    for _ in range(2):
+        qsv.sv_simulate(a, c, init_kind=qsv.INIT_PLUS, opts=o, norm_out=norm, bitstrings=bits if m else None,
+                        amps_out=out if m else None)
+    s = a.cpu().numpy().astype(np.complex128)
+    want = float(np.sum(s.real ** 2 + s.imag ** 2))
+    assert abs(float(norm[0]) - want) <= 2 * 2.0 ** 8 * 2.0 ** -53 * want
+    if m:
+        assert torch.equal(out, a[bits])
