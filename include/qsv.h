@@ -514,8 +514,12 @@ qsv_status sv_branch_combine_full(const void *a_states, const void *b_states, si
  * shape tuned for their class (sv_tune / sv_tune_set); in the captured graph
  * the passes of each such plan and the rounds of each tile shape are a branch
  * of their own, so independent states run side by side (the batch makes four
- * side streams for the capture when it has two or more branches).  There is
- * no persistent form: QSV_BATCH_PERSISTENT=1 makes sv_batch_create return
+ * side streams for the capture when it has two or more branches).  Entries
+ * of one circuit that start from |+>^n share the part of it that runs before
+ * the branch bits they differ in (compiled plans; up to 64 MiB of device
+ * memory per plan for the shared states, held until the batch is destroyed).
+ * There is no persistent
+ * form: QSV_BATCH_PERSISTENT=1 makes sv_batch_create return
  * QSV_EUNSUPPORTED.
  *
  * sv_batch_create: count entries; entry i runs circuit circs[i] with branch

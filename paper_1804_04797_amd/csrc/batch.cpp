@@ -28,6 +28,8 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <memory>
+#include <set>
 #include <vector>
 
 #include "jit.h"
@@ -43,13 +45,27 @@ struct BatchShape {
     qsv::BatchSeg *d_segs = nullptr;             // into the batch's table block
 };
 
+// One launch of a compiled plan: a pass over count rows of the plan's table.
+struct BatchStep {
+    size_t pass, first, count;
+};
+// Row of that table: the pass reads state src and writes state dst for the
+// branch of an entry (position in the plan's group).  States below the group's
+// size are the entries' own, the others the plan's scratch.
+struct BatchRow {
+    uint32_t entry, dst, src;
+};
+
 struct qsv_batch {
     int R = 0, T = 0, c = 0;
     bool forced_shape = false;  // opts gave a tile shape: every generic entry uses it
     int jit_mode = 0;  // opts->jit: 1 always, -1 never, 0 for plans shared by >= 8 entries
     std::vector<std::vector<uint32_t>> group;       // entries of each plan
     std::vector<char> plan_jit;                     // plan runs as compiled kernels
-    std::vector<qsv::BatchEntry *> d_group_ents;    // per compiled plan: its entries' table
+    std::vector<char *> d_scratch;                  // states that a plan's entries share, or null
+    std::vector<std::vector<BatchRow>> rows;        // per compiled plan: rows of its steps
+    std::vector<std::vector<BatchStep>> steps;      // and its launches, in order
+    std::vector<qsv::BatchEntry *> d_group_ents;    // per compiled plan: its rows' table
     std::vector<const qsv_circuit *> circs;
     std::vector<uint64_t> branches;
     // built for the layer range of the current run
@@ -87,6 +103,9 @@ void free_tables(qsv_batch *b) {
     for (auto *p : b->d_group_ents)
         if (p) hipFree(p);
     b->d_group_ents.clear();
+    for (char *p : b->d_scratch)
+        if (p) hipFree(p);
+    b->d_scratch.clear();
     if (b->d_progs) hipFree(b->d_progs);
     if (b->d_ents) hipFree(b->d_ents);
     if (b->d_tabs) hipFree(b->d_tabs);
@@ -114,6 +133,17 @@ constexpr int kLdsState = 14;
 // entries that share a plan from which on its kernels are compiled
 constexpr size_t kSharedPlan = 8;
 bool big_state(const qsv_batch *b, int n) { return b->jit_mode >= 0 && n >= kBigState; }
+// most scratch of a plan for states that entries share; larger ones stay in the
+// entries' own buffers, for one more launch where they are overwritten
+constexpr size_t kShareScratch = size_t(64) << 20;
+// states of 15 qubits from which on each is held by one tile: one for each CU
+constexpr size_t kWholeStates = 256;
+// entries of one launch of a compiled pass (grid rows)
+constexpr size_t kGridRows = 65536;
+// whether a plan of n qubits with count entries runs as compiled passes
+bool compiled(const qsv_batch *b, int n, size_t count) {
+    return (b->jit_mode > 0 || (b->jit_mode == 0 && (count >= kSharedPlan || big_state(b, n)))) && count < kGridRows;
+}
 
 // Tile shape (R, T) with R + T = n for a state held by one tile.
 bool lds_shape(int n, int *R, int *T) {
@@ -153,6 +183,148 @@ void make_schedule(const std::vector<int> &n, const std::vector<size_t> &np, con
     }
 }
 
+// Branch bits that a pass depends on.
+uint64_t branch_bits(const PassProg &p) {
+    uint64_t m = 0;
+    for (int pc = 0; pc < p.n_ops; ++pc) {
+        const uint64_t op = p.ops[pc];
+        const uint32_t code = uint32_t(op & 0xff), b = uint32_t((op >> 16) & 0xff), c = uint32_t((op >> 24) & 0xff);
+        if (code == OP_XCHG) ++pc;
+        else if (code == OP_ZB || (code == OP_PROJ && c)) m |= 1ull << (b & 63);
+    }
+    return m;
+}
+
+// Values that the given bits take in the branches.
+size_t distinct(const std::vector<uint64_t> &branches, uint64_t bits) {
+    std::set<uint64_t> v;
+    for (uint64_t x : branches) v.insert(x & bits);
+    return v.size();
+}
+
+// Entries that differ in their branches only and start from the same state are
+// the same state up to the first gate that takes the bits they differ in: it is
+// computed once and read from there.  What bounds batched compiled passes is
+// their arithmetic, so the gain is the gates not applied again (2 x 1024 branch
+// states of 15 qubits, five of ten branch bits after half of the layers: 336 ->
+// 238 us).  Only where the entries' tiles are more than the CUs hold at once (two
+// each): below, a pass takes the time of one tile, and the extra launches would
+// only be added.
+bool sharing_pays(size_t count, uint64_t tiles) { return tiles * count > 512; }
+
+// Branch level at which the circuit is cut in two plans, so that the first one
+// runs for few states: the cut with the fewest gates over all states, if that
+// saves a quarter of them; 0: none.
+int shared_levels(const qsv_circuit &c, int lb, const std::vector<uint64_t> &branches) {
+    std::vector<int> lev;
+    std::vector<uint64_t> bits;
+    branch_levels(c, lev, bits);
+    std::vector<double> gates(bits.size() + 1, 0.0);
+    double total = 0, before = 0;
+    for (size_t i = 0; i < lev.size(); ++i)
+        if (c.gates[i].layer >= lb) ++gates[size_t(lev[i])], ++total;
+    const double count = double(branches.size());
+    double best = 0.75 * count * total;
+    uint64_t known = 0;
+    int cut = 0;
+    for (size_t l = 1; l <= bits.size(); ++l) {
+        before += gates[l - 1];
+        if (l > 1) known |= bits[l - 2];
+        if (before == 0 || before == total) continue;
+        const double cost = double(distinct(branches, known)) * before + count * (total - before);
+        if (cost < best) {
+            best = cost;
+            cut = int(l);
+        }
+    }
+    return cut;
+}
+
+// The launches of a compiled plan.  After pass p one state
+// stands for the entries with the same values of the branch bits of passes 0..p:
+// in scratch where max_scratch states are enough, otherwise that of the first
+// entry.  Pass p + 1 reads it there for each of them, those that write elsewhere
+// first, then those that overwrite what was read.  The last pass writes every
+// entry.  A pass is shared when that halves its states or more.
+void share_passes(const Plan &plan, const std::vector<uint64_t> &branches, bool share,
+                  size_t max_scratch, std::vector<BatchRow> &rows, std::vector<BatchStep> &steps, size_t *scratch) {
+    const size_t np = plan.passes.size(), count = branches.size();
+    std::vector<std::vector<uint32_t>> first;  // per shared pass: the first entry with an entry's bits
+    uint64_t bits = 0;
+    size_t states = 0;
+    for (size_t p = 0; share && p + 1 < np; ++p) {
+        bits |= branch_bits(plan.passes[p].prog);
+        std::map<uint64_t, uint32_t> rep;
+        for (size_t i = 0; i < count; ++i) rep.emplace(branches[i] & bits, uint32_t(i));
+        if (rep.size() * 2 > count) break;
+        states = rep.size();
+        first.emplace_back(count);
+        for (size_t i = 0; i < count; ++i) first.back()[i] = rep[branches[i] & bits];
+    }
+    // where the first entries' states are (the last shared pass has them all)
+    std::vector<uint32_t> slot(count);
+    *scratch = states <= max_scratch ? states : 0;
+    uint32_t used = 0;
+    for (size_t i = 0; i < count; ++i)
+        slot[i] = *scratch && first.back()[i] == i ? uint32_t(count) + used++ : uint32_t(i);
+    std::vector<uint32_t> at(count), next(count);  // where an entry's state is, before and after the pass
+    for (size_t i = 0; i < count; ++i) at[i] = first.empty() ? uint32_t(i) : slot[first[0][i]];
+    for (size_t p = 0; p < np; ++p) {
+        std::vector<BatchRow> away, in_place;
+        for (size_t i = 0; i < count; ++i) {
+            const bool shared = p < first.size();
+            next[i] = shared ? slot[first[p][i]] : uint32_t(i);
+            if (!shared || first[p][i] == i)
+                (at[i] == next[i] ? in_place : away).push_back({uint32_t(i), next[i], at[i]});
+        }
+        // siblings side by side: they read the same tiles
+        std::stable_sort(away.begin(), away.end(), [](const BatchRow &x, const BatchRow &y) { return x.src < y.src; });
+        for (const auto *part : {&away, &in_place}) {
+            if (part->empty()) continue;
+            steps.push_back({p, rows.size(), part->size()});
+            rows.insert(rows.end(), part->begin(), part->end());
+        }
+        at = next;
+    }
+}
+
+// The circuit's plan from layer lb on in tile shape sh.  With cut > 0 the passes
+// of the branch levels below it come before those of the others (each ends in
+// the natural order of the qubits, so they follow one another); the plan's key
+// then has a first layer of -cut (this only occurs with lb = 1).
+qsv_status batch_plan(qsv_circuit *c, int lb, int cut, const TileShape &sh, std::shared_ptr<Plan> &p) {
+    const PlanKey key{cut ? -cut : lb, -1, sh.R, sh.T, sh.c, false};
+    {
+        std::lock_guard<std::mutex> g(c->mu);
+        auto pit = c->plans.find(key);
+        if (pit != c->plans.end()) {
+            p = pit->second;
+            return QSV_OK;
+        }
+    }
+    auto made = std::make_shared<Plan>();
+    qsv_status st = QSV_OK;
+    if (!cut) {
+        st = build_plan(*c, lb, -1, sh, *made);
+    } else {
+        int levels = 0;
+        st = circuit_branch_levels(c, &levels, nullptr, 0);
+        for (int part = 0; part < 2 && st == QSV_OK; ++part) {
+            qsv_circuit *out = nullptr;
+            st = circuit_branch_stage(c, part ? cut : 0, part ? levels + 1 : cut, &out);
+            if (st != QSV_OK) break;
+            const std::unique_ptr<qsv_circuit, void (*)(qsv_circuit *)> stage(out, circuit_destroy);
+            Plan half;
+            st = build_plan(*stage, lb, -1, sh, part ? half : *made);
+            for (Pass &pass : half.passes) made->passes.push_back(std::move(pass));
+        }
+    }
+    if (st != QSV_OK) return st;
+    std::lock_guard<std::mutex> g(c->mu);
+    p = c->plans.emplace(key, made).first->second;
+    return QSV_OK;
+}
+
 // Plans and device tables for layers [lb, end) of every entry.
 qsv_status build_tables(qsv_batch *b, int lb) {
     drop_graph(b);
@@ -160,8 +332,8 @@ qsv_status build_tables(qsv_batch *b, int lb) {
     b->plans.clear();
     b->entry_plan.assign(b->circs.size(), 0);
     std::map<const qsv_circuit *, uint32_t> idx;
-    std::map<const qsv_circuit *, size_t> sharers;
-    for (const qsv_circuit *c : b->circs) ++sharers[c];
+    std::map<const qsv_circuit *, std::vector<uint64_t>> sharers;  // the branches of each circuit
+    for (size_t i = 0; i < b->circs.size(); ++i) sharers[b->circs[i]].push_back(b->branches[i]);
     std::vector<TileShape> plan_shape;
     for (size_t i = 0; i < b->circs.size(); ++i) {
         auto it = idx.find(b->circs[i]);
@@ -186,26 +358,24 @@ qsv_status build_tables(qsv_batch *b, int lb) {
                 }
             } else if (!b->forced_shape && c->n <= kLdsState && lds_shape(c->n, &lr, &lt)) {
                 sh = TileShape{lr, lt, std::min(5, lt + 1)};
-            } else if (!b->forced_shape && b->jit_mode >= 0 && (b->jit_mode > 0 || sharers[c] >= kSharedPlan)) {
+            } else if (!b->forced_shape && b->jit_mode >= 0 &&
+                       (b->jit_mode > 0 || sharers[c].size() >= kSharedPlan)) {
                 // compiled passes over many states fill the device anyway, and
                 // the larger tile has fewer exchanges (2 x 1024 branch states
-                // of 15 qubits: 315 us against 387 us on (4, 8, 4))
-                sh = TileShape{5, 8, 5};
+                // of 15 qubits, nothing shared: 315 us against 387 us on (4, 8,
+                // 4)); with the whole state in one tile there is one pass over
+                // memory, not two (with shared prefixes: 238 us on (5, 10, 5)
+                // and (6, 9, 5), which takes longer to compile; 398 on (5, 8, 5))
+                const bool whole =
+                    c->n == 15 && sharers[c].size() >= kWholeStates && sharers[c].size() < kGridRows;
+                sh = whole ? TileShape{5, 10, 5} : TileShape{5, 8, 5};
             }
-            PlanKey key{lb, -1, sh.R, sh.T, sh.c, false};
+            const bool shared = compiled(b, c->n, sharers[c].size()) && lb == 1 &&
+                                sharing_pays(sharers[c].size(), 1ull << (c->n - sh.R - sh.T));
+            const int cut = shared ? shared_levels(*c, lb, sharers[c]) : 0;
             std::shared_ptr<Plan> p;
-            {
-                std::lock_guard<std::mutex> g(c->mu);
-                auto pit = c->plans.find(key);
-                if (pit != c->plans.end()) {
-                    p = pit->second;
-                } else {
-                    p = std::make_shared<Plan>();
-                    qsv_status st = build_plan(*c, lb, -1, sh, *p);
-                    if (st != QSV_OK) return st;
-                    c->plans[key] = p;
-                }
-            }
+            const qsv_status st = batch_plan(c, lb, cut, sh, p);
+            if (st != QSV_OK) return st;
             it = idx.emplace(b->circs[i], uint32_t(b->plans.size())).first;
             b->plans.push_back(p);
             plan_shape.push_back(sh);
@@ -216,15 +386,29 @@ qsv_status build_tables(qsv_batch *b, int lb) {
     for (size_t i = 0; i < b->circs.size(); ++i) b->group[b->entry_plan[i]].push_back(uint32_t(i));
     b->plan_jit.assign(b->plans.size(), 0);
     b->d_group_ents.assign(b->plans.size(), nullptr);
+    b->d_scratch.assign(b->plans.size(), nullptr);
+    b->rows.assign(b->plans.size(), {});
+    b->steps.assign(b->plans.size(), {});
     for (size_t p = 0; p < b->plans.size(); ++p) {
-        const bool shared = b->group[p].size() >= kSharedPlan;
-        const bool big = big_state(b, b->plans[p]->n);
-        b->plan_jit[p] = !b->plans[p]->passes.empty() &&
-                         (b->jit_mode > 0 || (b->jit_mode == 0 && (shared || big))) &&
-                         b->group[p].size() < 65536;
+        const Plan &plan = *b->plans[p];
+        b->plan_jit[p] = !plan.passes.empty() && compiled(b, plan.n, b->group[p].size());
         if (b->plan_jit[p]) {
+            std::vector<uint64_t> branches;
+            for (uint32_t i : b->group[p]) branches.push_back(b->branches[i]);
+            // from layer 1 on the run starts every entry from |+>^n
+            const bool share = lb == 1 && sharing_pays(branches.size(), 1ull << (plan.n - plan.R - plan.T));
+            const size_t bytes = sizeof(float2) << plan.n;
+            size_t scratch = 0;
+            share_passes(plan, branches, share, kShareScratch / bytes, b->rows[p], b->steps[p], &scratch);
+            if (scratch && hipMalloc(reinterpret_cast<void **>(&b->d_scratch[p]), scratch * bytes) != hipSuccess) {
+                (void)hipGetLastError();  // then in the entries' own states
+                b->d_scratch[p] = nullptr;
+                b->rows[p].clear();
+                b->steps[p].clear();
+                share_passes(plan, branches, share, 0, b->rows[p], b->steps[p], &scratch);
+            }
             hipError_t e = hipMalloc(reinterpret_cast<void **>(&b->d_group_ents[p]),
-                                     b->group[p].size() * sizeof(BatchEntry));
+                                     b->rows[p].size() * sizeof(BatchEntry));
             if (e != hipSuccess) return fail(QSV_ENOMEM, "sv_batch: group entry table");
         }
     }
@@ -396,7 +580,7 @@ qsv_status sv_batch_run(qsv_batch *b, void *const *amps_dev, int init_plus,
                       std::equal(b->g_ptrs.begin(), b->g_ptrs.end(), amps_dev);
     if (!same) {
         drop_graph(b);
-        for (size_t i = 0; i < count; ++i) b->h_ents[i].amps = amps_dev[i];
+        for (size_t i = 0; i < count; ++i) b->h_ents[i].src = b->h_ents[i].amps = amps_dev[i];
         // the previous graph may still read the entry table
         hipError_t e = hipStreamSynchronize(s);
         if (e != hipSuccess) return hipfail(e, "sv_batch_run");
@@ -407,7 +591,16 @@ qsv_status sv_batch_run(qsv_batch *b, void *const *amps_dev, int init_plus,
         for (size_t p = 0; p < b->plans.size(); ++p) {
             if (!b->plan_jit[p]) continue;
             std::vector<BatchEntry> ge;
-            for (uint32_t i : b->group[p]) ge.push_back(b->h_ents[i]);
+            for (const BatchRow &r : b->rows[p]) {
+                const auto state = [&](uint32_t k) -> void * {
+                    const size_t own = b->group[p].size();
+                    return k < own ? amps_dev[b->group[p][k]]
+                                   : b->d_scratch[p] + ((k - own) * sizeof(float2) << b->plans[p]->n);
+                };
+                ge.push_back(b->h_ents[b->group[p][r.entry]]);
+                ge.back().amps = state(r.dst);
+                ge.back().src = state(r.src);
+            }
             e = hipMemcpy(b->d_group_ents[p], ge.data(), ge.size() * sizeof(BatchEntry),
                           hipMemcpyHostToDevice);
             if (e != hipSuccess) return hipfail(e, "sv_batch_run: group entry upload");
@@ -440,9 +633,7 @@ qsv_status sv_batch_run(qsv_batch *b, void *const *amps_dev, int init_plus,
             size_t plan, shape;  // shape == ~0: compiled plan
         };
         std::vector<Chain> chains;
-        for (size_t p : jp)
-            chains.push_back({double(b->group[p].size()) * std::ldexp(double(b->plans[p]->passes.size()), b->plans[p]->n),
-                              p, ~size_t(0)});
+        for (size_t p : jp) chains.push_back({std::ldexp(double(b->rows[p].size()), b->plans[p]->n), p, ~size_t(0)});
         for (size_t k = 0; k < b->shapes.size(); ++k) {
             double blocks = 0;
             for (uint64_t x : b->shapes[k].round_blocks) blocks += double(x);
@@ -499,9 +690,11 @@ qsv_status sv_batch_run(qsv_batch *b, void *const *amps_dev, int init_plus,
             const hipStream_t ls = k < joined ? b->lanes[k] : b->cap;
             load[k] += ch.work;
             if (ch.shape == ~size_t(0)) {
-                if (jit_launch_batched(*b->plans[ch.plan], variant, b->d_group_ents[ch.plan],
-                                       unsigned(b->group[ch.plan].size()), ls) != QSV_OK)
-                    le = hipErrorLaunchFailure;
+                for (const BatchStep &sp : b->steps[ch.plan])
+                    if (le == hipSuccess &&
+                        jit_launch_batched(*b->plans[ch.plan], variant, sp.pass, b->d_group_ents[ch.plan] + sp.first,
+                                           unsigned(sp.count), ls) != QSV_OK)
+                        le = hipErrorLaunchFailure;
                 continue;
             }
             const BatchShape &bs = b->shapes[ch.shape];

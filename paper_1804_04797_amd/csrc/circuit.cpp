@@ -236,6 +236,11 @@ static void branch_levels(const qsv_circuit &c, std::vector<int> &lev, std::vect
     }
 }
 
+void qsv::branch_levels(const qsv_circuit &c, std::vector<int> &lev, std::vector<uint64_t> &bits) {
+    std::vector<int> layers;
+    ::branch_levels(c, lev, layers, bits);
+}
+
 extern "C" qsv_status circuit_branch_levels(const qsv_circuit *c, int *n_levels, uint64_t *level_bits,
                                             size_t cap) {
     if (!c || !n_levels) return fail(QSV_EINVAL, "circuit_branch_levels: null argument");

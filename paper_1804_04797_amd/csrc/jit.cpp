@@ -53,6 +53,7 @@ struct SampleTabJ {  // layout of the library's sampling table
 };
 struct BatchEntryJ {  // layout of the library's batch entry table
     void *amps;
+    const void *src;
     unsigned long long branch;
     unsigned prog0, n;
     float init_val;
@@ -1020,7 +1021,7 @@ struct Gen {
             o << "(const BatchEntryJ* __restrict__ ents, unsigned long long tile0) {\n";
             o << "const BatchEntryJ en = ents[blockIdx.y];\n";
             o << CT << "* a = (" << CT << "*)en.amps;\n";
-            o << "const " << CT << "* srcp = a;\n";
+            o << "const " << CT << "* srcp = (const " << CT << "*)en.src;\n";
             o << "const unsigned long long branch = en.branch, basis = 0ull;\n";
             o << "double* part = nullptr;\n";
         } else if (sample_rows) {
@@ -1433,7 +1434,7 @@ qsv_status jit_launch(const Plan &plan, int variant, void *amps, void *scratch, 
     return QSV_OK;
 }
 
-qsv_status jit_launch_batched(const Plan &plan, int variant, const void *ents, unsigned count,
+qsv_status jit_launch_batched(const Plan &plan, int variant, size_t pass, const void *ents, unsigned count,
                               hipStream_t s) {
     auto vit = plan.jit_variants.find(variant);
     if (vit == plan.jit_variants.end()) return fail(QSV_EINTERNAL, "jit variant not prepared");
@@ -1441,17 +1442,15 @@ qsv_status jit_launch_batched(const Plan &plan, int variant, const void *ents, u
     const int L = plan.R + plan.T;
     const uint64_t tiles = 1ull << (plan.n - L);
     const uint64_t chunk = 1ull << 30;
-    for (size_t p = 0; p < plan.passes.size(); ++p) {
-        for (uint64_t t0 = 0; t0 < tiles; t0 += chunk) {
-            const uint64_t cnt = (tiles - t0 < chunk) ? tiles - t0 : chunk;
-            const void *en = ents;
-            unsigned long long tt = t0;
-            void *args[] = {&en, &tt};
-            hipError_t he = hipModuleLaunchKernel(e.fns[p], unsigned(cnt), count, 1, 1u << plan.T, 1, 1,
-                                                  unsigned(e.lds[p]), s, args, nullptr);
-            if (he != hipSuccess)
-                return fail(QSV_EHIP, std::string("hipModuleLaunchKernel: ") + hipGetErrorString(he));
-        }
+    for (uint64_t t0 = 0; t0 < tiles; t0 += chunk) {
+        const uint64_t cnt = (tiles - t0 < chunk) ? tiles - t0 : chunk;
+        const void *en = ents;
+        unsigned long long tt = t0;
+        void *args[] = {&en, &tt};
+        hipError_t he = hipModuleLaunchKernel(e.fns[pass], unsigned(cnt), count, 1, 1u << plan.T, 1, 1,
+                                              unsigned(e.lds[pass]), s, args, nullptr);
+        if (he != hipSuccess)
+            return fail(QSV_EHIP, std::string("hipModuleLaunchKernel: ") + hipGetErrorString(he));
     }
     return QSV_OK;
 }

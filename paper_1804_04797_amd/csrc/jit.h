@@ -62,7 +62,7 @@ qsv_status jit_launch(const Plan &plan, int variant, void *amps, void *scratch, 
                       uint64_t sample_tiles = 0, void *sample_out = nullptr, uint64_t sample_rows = 1,
                       uint64_t sample_stride = 0, uint64_t max_tiles = 0);
 // Launch all passes over `count` batch entries (BatchEntry table on the device).
-qsv_status jit_launch_batched(const Plan &plan, int variant, const void *ents, unsigned count,
+qsv_status jit_launch_batched(const Plan &plan, int variant, size_t pass, const void *ents, unsigned count,
                               hipStream_t s);
 // Compile without loading (no device needed).
 qsv_status jit_compile_only(const Plan &plan, size_t *code_bytes, double *seconds);

@@ -64,6 +64,7 @@ static_assert(sizeof(PassProg) == 8 * kMaxOps + 2 * kMaxSlots + 96 + 16, "PassPr
 // Device-side tables of a batch (batch.cpp).
 struct BatchEntry {
     void *amps;         // state of the entry (complex64[2^n])
+    const void *src;    // compiled passes: the state a pass reads (amps, or a sibling's)
     uint64_t branch;    // branch index of PB/ZB gates
     uint32_t prog0;     // index of the entry's first pass program
     uint32_t n;         // qubits
@@ -185,6 +186,9 @@ bool gate_is_diagonal(uint8_t kind);
 bool gate_is_single(uint8_t kind);
 qsv_status generate_lattice_circuit(int rows, int cols, const uint8_t *present, int depth,
                                     uint64_t seed, qsv_circuit *out);
+
+// level of every gate and branch bits of levels 1, 2, ... (circuit_branch_levels)
+void branch_levels(const qsv_circuit &c, std::vector<int> &lev, std::vector<uint64_t> &bits);
 
 // planner.cpp
 // oop: every pass but the first reads one buffer and writes the other, so a
