@@ -320,8 +320,8 @@ qsv_status sv_simulate_c128(void *amps, const qsv_circuit *c, uint64_t branch, i
  * share every gate before their first differing cut, so the state at a cut
  * layer is computed once and each child continues from it.  src, dst:
  * device complex64[2^n], 16-byte aligned, must not overlap (src == dst runs
- * in place).  With the generic kernel (jit = -1) or the per-gate path, src
- * is copied to dst first.  workspace / ws_bytes as for sv_apply_fused.
+ * in place).  With the generic kernel (jit = -1) the first launch reads src;
+ * with the per-gate path src is copied to dst first.  workspace / ws_bytes as for sv_apply_fused.
  * Asynchronous on stream.
  */
 qsv_status sv_apply_fused_from(const void *src, void *dst, const qsv_circuit *c, uint64_t branch,
@@ -452,7 +452,7 @@ qsv_status sv_norm_fp64(const void *amps, int n_qubits, double *out_dev, void *s
  * The call allocates nothing (no hipMalloc, hipFree or allocating library
  * routine).  Calls that overlap on one device share that array and race:
  * serialise them (one stream, or events between streams).  n_qubits <= 34
- * (QSV_ERANGE otherwise); the state needs at most 65536 partials at any n.
+ * (QSV_ERANGE otherwise); the state needs at most 8192 partials at any n.
  */
 qsv_status sv_norm_fp64_noalloc(const void *amps, int n_qubits, double *out_dev, void *stream);
 
@@ -482,7 +482,8 @@ qsv_status sv_branch_combine(const void *a_tab, const void *b_tab, size_t n_bran
  * eq. (1), eqs. (6)-(7)): out[x] = s(x) * sum_b A_b[x_A] B_b[x_B] for all
  * 2^(n_a + n_b) indices x, a complex GEMM on matrix cores.  flags = 0: the
  * complex64 inputs are widened to FP64 and every product and sum is FP64
- * (v_mfma_f64_16x16x4f64), the result rounded once to a complex64 out_state;
+ * (v_mfma_f64_16x16x4f64, three real products per complex one: an infinite
+ * or NaN input gives NaN), the result rounded once to a complex64 out_state;
  * QSV_COMBINE_OUT_C128: out_state is complex128 (no rounding);
  * QSV_COMBINE_FP32: FP32 products and accumulation on FP32 matrix cores
  * (twice the rate, FP32 rounding in the sums).  a_states: complex64
@@ -518,9 +519,8 @@ qsv_status sv_branch_combine_full(const void *a_states, const void *b_states, si
  * of one circuit that start from |+>^n share the part of it that runs before
  * the branch bits they differ in (compiled plans; up to 64 MiB of device
  * memory per plan for the shared states, held until the batch is destroyed).
- * There is no persistent
- * form: QSV_BATCH_PERSISTENT=1 makes sv_batch_create return
- * QSV_EUNSUPPORTED.
+ * There is no persistent form: QSV_BATCH_PERSISTENT=1 makes sv_batch_create
+ * return QSV_EUNSUPPORTED.
  *
  * sv_batch_create: count entries; entry i runs circuit circs[i] with branch
  * index branch_ids[i] (NULL = all 0) on its own state.  Plans per circuit
@@ -607,9 +607,9 @@ qsv_status sv_debug_emulate(void *amps_host, const qsv_circuit *c, uint64_t bran
                             int layer_begin, int layer_end, const qsv_fuse_opts *opts);
 
 /*
- * sv_debug_batch_schedule - host emulation of the work-item schedule of a
- * persistent batch launch (a CPU check of its ordering rule; no product entry
- * point calls it): count entries of n_qubits[i] qubits and passes[i] passes on
+ * sv_debug_batch_schedule - host emulation of the batch's pass rounds as one
+ * ordered list of work items (a CPU check of their ordering rule; no product
+ * entry point calls it): count entries of n_qubits[i] qubits and passes[i] passes on
  * tiles of 2^tile_qubits amplitudes, `workers` virtual workgroups taking the
  * items in order, completions in a seeded random order.  QSV_OK if every
  * (entry, pass, tile) runs exactly once, none starts before every tile of its

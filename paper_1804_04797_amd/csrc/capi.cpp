@@ -1113,7 +1113,9 @@ qsv_status sv_simulate(void *amps, const qsv_circuit *c, uint64_t branch, int in
         // generic kernel or per-gate path: init, sweep in place, then the
         // norm's partial sums in the workspace, from the last program or, where
         // the tiles are more than the reduction's own blocks, from that
-        const size_t need = norm_out_dev ? norm_partial_count(c->n) * sizeof(double) : 0;
+        // (the workspace asked for is that of sv_workspace_bytes' smallest, more
+        // than the partial sums themselves take)
+        const size_t need = norm_out_dev && c->n >= 14 ? sizeof(double) << std::min(c->n - 11, 16) : 0;
         if (need && (!ws.p || ws.bytes < need))
             return fail(QSV_EINVAL, "sv_simulate: the FP64 norm needs a workspace of sv_workspace_bytes bytes");
         hipError_t e = hipSuccess;

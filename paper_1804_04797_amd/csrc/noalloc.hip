@@ -21,9 +21,8 @@
 namespace qsv {
 namespace {
 
-// The norm of a state of 2^n amplitudes uses min(2^(n - 11), 65536)
-// partials (one per block of 1024 quads); states below 2^14 amplitudes use
-// none.
+// The norm of a state of 2^n amplitudes uses min(2^(n - 11), 8192) partials
+// (one per block of 1024 quads or more); states below 2^14 amplitudes use none.
 constexpr size_t kNoallocPartials = 65536;
 
 static __device__ __align__(256) double scratch[kNoallocPartials];
