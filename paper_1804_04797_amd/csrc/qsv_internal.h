@@ -77,14 +77,12 @@ struct BatchSeg {
     uint32_t pad;
 };
 
-// Persistent batch launch (one per tile shape of the generic kernel): work
-// items are ordered by pass round, then by entry, then by tile; a workgroup
-// takes the next item from a device counter.  Item i of round r is tile
-// (i - item_start - seg.start) of entry seg.entry, for the round's last
-// segment with start <= i - item_start.  An item of round r > 0 waits until
-// its entry has completed r * tiles(entry) items (every tile of its earlier
-// passes); it only ever waits on items taken before it, which are held by
-// running workgroups, so the launch cannot deadlock.
+// Rounds of a tile shape of the generic kernel: work items are ordered by pass
+// round, then by entry, then by tile; one launch per round.  Item i of round r
+// is tile (i - item_start - seg.start) of entry seg.entry, for the round's last
+// segment with start <= i - item_start.  Taken as one ordered list, an item of
+// round r > 0 would wait until its entry has completed r * tiles(entry) items
+// (every tile of its earlier passes): it only ever waits on items before it.
 struct BatchRound {
     uint64_t item_start;  // first item of the round
     uint32_t seg_off;     // its segments in the segment table

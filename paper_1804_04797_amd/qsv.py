@@ -425,7 +425,7 @@ def sv_batch_abort(batch):
 
 
 def sv_debug_batch_schedule(n_qubits, passes, tile_qubits, workers, seed=1, planted_early_start=False) -> int:
-    """Host emulation of a persistent batch launch's schedule; returns the
+    """Host emulation of a batch's pass rounds as one list of work items; returns the
     number of work items (raises if the ordering rule is violated)."""
     nq = np.ascontiguousarray(np.asarray(n_qubits, dtype=np.int32))
     pp = np.ascontiguousarray(np.asarray(passes, dtype=np.int32))
