@@ -10,15 +10,16 @@
 //  - larger states below 2^21 amplitudes: the batch's tile shape;
 //  - states of 2^21 amplitudes or more: compiled kernels of their own plan
 //    on the tile shape autotuned for their class (one launch per plan and
-//    pass, all entries of the plan in its grid).
+//    pass, all entries of the plan in its grid); a plan that kSharedPlan
+//    entries or more share is compiled at any size, and states that its
+//    entries share are computed once (share_passes).
 // The generic-kernel classes run as one launch per tile shape and program
 // round (a pass is one program, a very long one several), ordered by kernel
 // boundaries.  The schedule of a persistent form (work items (pass round,
 // entry, tile) taken in order from a device counter, BatchRound) is kept for
 // its host check; its kernel did not finish on the device and is gone.  The
-// launches
-// and the closing gather of every entry's sampled amplitudes are captured
-// once into a hipGraph and replayed: one graph launch per run.
+// launches and the closing gather of every entry's sampled amplitudes are
+// captured once into a hipGraph and replayed: one graph launch per run.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
