@@ -1053,14 +1053,16 @@ struct Gen {
             if (init_kind >= 0) emit_init(init_kind, n, tld);
             else emit_load("v", "base", tld);
         } else if (!loop) {
-            // Workgroups are dealt to the 8 XCDs in turn.  From 2^27 amplitudes
-            // on each XCD walks an eighth of the tiles instead of every eighth
-            // tile, so that the pages it has open and translated are its own
-            // (28 qubits, 3 passes: 2637 -> 2378 us; 30 qubits, 5 passes: 16.26
-            // -> 15.53 ms; 26 qubits, 4 passes: 829 -> 846 us).
+            // Workgroups are dealt to the 8 XCDs in turn.  From 2^27 to 2^31
+            // amplitudes each XCD walks an eighth of the tiles instead of every
+            // eighth tile, so that the pages it has open and translated are its
+            // own (28 qubits, 3 passes: 2637 -> 2378 us; 30 qubits, 5 passes: 16.26
+            // -> 15.53 ms; 31 qubits: 32.9 -> 31.7; 26 qubits, 4 passes: 829 -> 846
+            // us).  Above, it depends on the passes (tile (5, 8, 4): 32 qubits 63.5
+            // -> 65.2 ms, 34 qubits, depth 16, 237 -> 226, depth 30, 284 -> 298).
             // The tile count is a literal: a gridDim in the expression changes how
             // the compiler orders sums further down, and with it their rounding.
-            if (n >= 27)
+            if (n >= 27 && n <= 31)
                 o << "const unsigned long long tile = tile0 + (((blockIdx.x & 7u) << " << (n - L - 3)
                   << ") + (blockIdx.x >> 3));\n";
             else o << "const unsigned long long tile = tile0 + blockIdx.x;\n";
