@@ -48,7 +48,7 @@ struct Lower {
     bool open_h1 = false;    // the last op is a Hadamard that another may join
     const bool gate_order;
     int ahead = 0;           // at most so many ops follow up to the next exchange
-    bool e_dirty = false;    // gate order: e holds T gates not multiplied in yet
+    bool e_dirty = false;    // e holds phases not multiplied in yet
 
     Lower(const Plan &p, bool ordered, std::vector<GenProg> &o)
         : plan(p), out(o), R(p.R), T(p.T), L(p.R + p.T), n(p.n), W(gen_weights(p.R, p.T)),
@@ -270,6 +270,7 @@ struct Lower {
             g.w[0] |= uint32_t(p.l) << 8 | locator(q) << 16;
             g.w[3] = thread_mask(p.cz);
             g.w[4] = tile_mask(p.cz);
+            e_dirty = true;  // a split before the next one multiplies it in
             clear(q);
         }
     }
