@@ -1331,17 +1331,32 @@ qsv_status sv_debug_emulate(void *amps_host, const qsv_circuit *c, uint64_t bran
     float *amps = static_cast<float *>(amps_host);
     if (!jit_mode(c, opts) && fused_shape_supported(sh.R, sh.T)) {  // the generic kernel's programs
         std::shared_ptr<const std::vector<GenProg>> progs;
-        // sv_simulate's programs on a copy: both forms are checked
+        // sv_simulate's programs on a copy, on the tile that it takes: both
+        // forms are checked
+        TileShape so;
+        std::shared_ptr<Plan> in_order;
+        if ((st = resolve_shape(c, opts, so, layer_begin, layer_end, true)) != QSV_OK) return st;
+        if ((st = get_plan(c, layer_begin, layer_end, so, in_order)) != QSV_OK) return st;
         std::vector<float> ordered(amps, amps + (size_t(2) << c->n));
-        float most = 0.f;  // largest component of the start: no gate makes a state longer
-        for (float x : ordered) most = std::max(most, std::fabs(x));
-        if ((st = generic_programs(*plan, true, progs)) != QSV_OK) return st;
-        for (const GenProg &p : *progs) emulate_gen(p, c->n, sh.R, sh.T, branch, ordered.data());
+        double norm2 = 0.0, diff2 = 0.0;
+        for (float x : ordered) norm2 += double(x) * double(x);
+        if ((st = generic_programs(*in_order, true, progs)) != QSV_OK) return st;
+        for (const GenProg &p : *progs) emulate_gen(p, c->n, so.R, so.T, branch, ordered.data());
         if ((st = generic_programs(*plan, false, progs)) != QSV_OK) return st;
         for (const GenProg &p : *progs) emulate_gen(p, c->n, sh.R, sh.T, branch, amps);
-        for (size_t i = 0; i < ordered.size(); ++i)
-            if (!(std::fabs(ordered[i] - amps[i]) <= 1e-5f * most)) 
-                return fail(QSV_EINTERNAL, "sv_debug_emulate: the lowered forms differ");
+        // No gate makes the state longer in the 2-norm, and a gate's roundings
+        // are off by at most 4 * 2^-24 of its length in either form (T: the
+        // rounded sqrt(1/2), the sum and the product); the closing scale counts
+        // as one more.  States whose intermediate values may leave the range of
+        // FP32 are not compared.
+        if (!(norm2 >= 0x1p-40 && norm2 <= 0x1p40)) return QSV_OK;
+        for (size_t i = 0; i < ordered.size(); ++i) {
+            const double d = double(ordered[i]) - double(amps[i]);
+            diff2 += d * d;
+        }
+        const double bound = 2 * 4 * 0x1p-24 * (double(plan->gate_range.size()) + 1.0);
+        if (!(diff2 <= bound * bound * norm2))
+            return fail(QSV_EINTERNAL, "sv_debug_emulate: the lowered forms differ");
         return QSV_OK;
     }
     // the same buffer schedule as the device sweep
