@@ -299,12 +299,15 @@ int jit_mode(const qsv_circuit *c, const qsv_fuse_opts *opts) {
     return j >= 2 ? (1 | kJitLoop) : 1;
 }
 
-// Tile shape of a call: the options' one, else the default.
+// Tile shape of a call: the options' one, else the default.  Options that name
+// some of the shape are completed from the largest-tile default in every call,
+// so that all entry points take and refuse the same ones.
 qsv_status resolve_shape(const qsv_circuit *c, const qsv_fuse_opts *opts, TileShape &sh, int lb, int le,
                          bool gate_order = false) {
-    sh = default_shape(c->n, gate_order);
+    const bool named = opts && (opts->reg_qubits || opts->thread_qubits || opts->low_qubits);
+    sh = default_shape(c->n, gate_order || named);
     const int jm = jit_mode(c, opts);
-    if (!gate_order && jm && !(opts && (opts->reg_qubits || opts->thread_qubits || opts->low_qubits))) {
+    if (!gate_order && jm && !named) {
         const qsv_status st = compiled_default_shape(c, lb, le, oop_mode(c, opts, jm) != 0, sh);
         if (st != QSV_OK) return st;
     }
