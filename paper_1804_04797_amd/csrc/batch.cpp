@@ -59,6 +59,7 @@ struct BatchRow {
 
 struct qsv_batch {
     int R = 0, T = 0, c = 0;
+    int low = 0;                // opts->low_qubits
     bool forced_shape = false;  // opts gave a tile shape: every generic entry uses it
     int jit_mode = 0;  // opts->jit: 1 always, -1 never, 0 for plans shared by >= 8 entries
     std::vector<std::vector<uint32_t>> group;       // entries of each plan
@@ -369,7 +370,8 @@ qsv_status build_tables(qsv_batch *b, int lb) {
                 // and (6, 9, 5), which takes longer to compile; 398 on (5, 8, 5))
                 const bool whole =
                     c->n == 15 && sharers[c].size() >= kWholeStates && sharers[c].size() < kGridRows;
-                sh = whole ? TileShape{5, 10, 5} : TileShape{5, 8, 5};
+                const int low = b->low ? b->low : 5;
+                sh = whole ? TileShape{5, 10, low} : TileShape{5, 8, low};
             }
             const bool shared = compiled(b, c->n, sharers[c].size()) && lb == 1 &&
                                 sharing_pays(sharers[c].size(), 1ull << (c->n - sh.R - sh.T));
@@ -538,7 +540,8 @@ qsv_status sv_batch_create(const qsv_circuit *const *circs, const uint64_t *bran
         if (!ok) return fail(QSV_EUNSUPPORTED, "sv_batch_create: no batch kernel for this tile shape");
         if (b->R + b->T > nmin) return fail(QSV_EUNSUPPORTED, "sv_batch_create: tile larger than a state");
     }
-    b->c = (opts && opts->low_qubits) ? opts->low_qubits : b->forced_shape ? std::min(5, b->T + 1) : 4;
+    b->low = opts ? opts->low_qubits : 0;
+    b->c = b->low ? b->low : b->forced_shape ? std::min(5, b->T + 1) : 4;
     b->jit_mode = opts ? opts->jit : 0;
     // There is no persistent launch (its kernel did not finish on the device):
     // asking for it is refused and every batch runs one launch per round.
