@@ -585,8 +585,9 @@ qsv_status sv_tune(void *amps_scratch, const qsv_circuit *c, int layer_begin, in
 qsv_status sv_tune_set(const qsv_circuit *c, int layer_begin, int layer_end, const qsv_fuse_opts *opts);
 
 /*
- * Plan inspection (host only, no device needed).  For the plan that
- * sv_apply_fused would use: *n_passes, and for each gate of the layer range
+ * Plan inspection (host only, no device needed).  For the plan that a call
+ * which does not work in place uses when its workspace holds a second state
+ * (sv_apply_fused_from): *n_passes, and for each gate of the layer range
  * the pass it runs in (pass_of_gate[i], -1 if outside the range) and its
  * position in that pass's program (order_in_pass[i]); resident_mask[p] is
  * the bit set of qubits resident in pass p (cap entries).  Arrays may be
@@ -628,6 +629,15 @@ qsv_status sv_debug_batch_schedule(const int *n_qubits, const int *passes, size_
  */
 qsv_status sv_debug_emulate_dense(void *amps_host, const qsv_circuit *c, uint64_t branch,
                                   int layer_begin, int layer_end, int k, int *n_blocks);
+
+/*
+ * sv_debug_fused_plan - the tile (tile[3] = reg, thread and low qubits) and
+ * the pass count of the plan that sv_apply_fused (in_place = 1) or
+ * sv_apply_fused_from (0) runs with a workspace of ws_bytes (host only, no
+ * device needed).
+ */
+qsv_status sv_debug_fused_plan(const qsv_circuit *c, int layer_begin, int layer_end, const qsv_fuse_opts *opts,
+                               int in_place, size_t ws_bytes, int *tile, int *n_passes);
 
 /*
  * sv_debug_jit_compile - generate and compile (no load, no device needed) the

@@ -347,7 +347,7 @@ qsv_status build_tables(qsv_batch *b, int lb) {
                 // states of the HBM-streaming class get their own compiled
                 // kernels with the single-state default tile shape
                 sh = default_shape(c->n);
-                const qsv_status shape_st = compiled_default_shape(c, lb, -1, false, sh);
+                const qsv_status shape_st = compiled_default_shape(c, lb, -1, 0, false, false, sh);
                 if (shape_st != QSV_OK) return shape_st;
                 // the autotuned shape of this circuit (sv_tune / sv_tune_set), if any
                 qsv_fuse_opts t;

@@ -183,6 +183,11 @@ qsv_status select_plan(const qsv_circuit *c, int lb, int le, TileShape sh, int o
     return get_plan(c, lb, le, sh, plan);
 }
 
+// whether the workspace holds a second state and part_need bytes
+bool holds_second(const qsv_circuit *c, const Workspace &ws, size_t part_need = 0) {
+    return ws.p && ws.bytes >= state_bytes(c->n) + part_need;
+}
+
 // Plan, second buffer and partial sums of a fused call.  part_need: bytes
 // of FP64 partial sums the call writes (0 = none).  An out-of-place plan
 // runs only when the workspace holds the second buffer and the partials;
@@ -192,19 +197,15 @@ qsv_status get_fused_plan(const qsv_circuit *c, int lb, int le, TileShape sh, in
                           std::shared_ptr<Plan> &plan, void **scratch, double **part) {
     *scratch = nullptr;
     if (part) *part = nullptr;
-    qsv_status st = select_plan(c, lb, le, sh, oop, reads_state, plan);
+    const bool second = holds_second(c, ws, part_need);
+    qsv_status st = select_plan(c, lb, le, sh, oop > 1 || second ? oop : 0, reads_state, plan);
     if (st != QSV_OK) return st;
     if (plan->oop) {
-        const size_t sb = state_bytes(c->n);
-        if (ws.p && ws.bytes >= sb + part_need) {
-            *scratch = ws.p;
-            if (part && part_need) *part = reinterpret_cast<double *>(ws.p + sb);
-            return QSV_OK;
-        }
-        if (oop > 1)
+        if (!second)
             return fail(QSV_EINVAL, "out-of-place sweep: the workspace is smaller than sv_workspace_bytes");
-        sh.oop = false;
-        if ((st = get_plan(c, lb, le, sh, plan)) != QSV_OK) return st;
+        *scratch = ws.p;
+        if (part && part_need) *part = reinterpret_cast<double *>(ws.p + state_bytes(c->n));
+        return QSV_OK;
     }
     if (part_need) {
         if (!ws.p || ws.bytes < part_need)
@@ -239,18 +240,24 @@ qsv_status get_plan(const qsv_circuit *cc, int lb, int le, TileShape sh,
 // the longer runs (28 qubits depth 14: 4 passes on (5, 8, 5) 3284 us, 3 on
 // (5, 8, 4) 2649 and on (5, 9, 5) 2602; 26 qubits depth 24: 5 passes 985, 4 on
 // (5, 8, 4) 828; equal counts: (5, 8, 5) 170, (5, 9, 5) 192 at 24 qubits).
+// What counts are the passes of the plan that the call runs: see get_fused_plan
+// for oop and reads_state; second: the workspace holds a second state.
 // The choice is remembered by the gates' hash (two circuits with one hash would
 // share a tile that fits both), so that another handle of a circuit plans one
 // tile only.
-qsv_status compiled_default_shape(const qsv_circuit *c, int lb, int le, bool oop, TileShape &sh) {
+qsv_status compiled_default_shape(const qsv_circuit *c, int lb, int le, int oop, bool reads_state, bool second,
+                                  TileShape &sh) {
     if (c->n < 24) return QSV_OK;
     static const int kTiles[][3] = {{5, 8, 5}, {5, 8, 4}, {5, 9, 5}, {5, 9, 4}};
     static std::mutex mu;
     static std::map<uint64_t, int> chosen;  // at most kKept entries
     constexpr size_t kKept = 4096;
+    if (oop == 1 && !second) oop = 0;
+    reads_state = reads_state && oop;
     uint64_t h = 0xcbf29ce484222325ull;  // FNV-1a over 64-bit words
     auto mix = [&h](uint64_t w) { h = (h ^ w) * 0x100000001b3ull; };
-    mix(uint64_t(c->n) | uint64_t(oop) << 8 | uint64_t(uint32_t(lb)) << 16 | uint64_t(uint16_t(le)) << 48);
+    mix(uint64_t(c->n) | uint64_t(oop != 0) << 8 | uint64_t(reads_state) << 9 | uint64_t(uint32_t(lb)) << 16 |
+        uint64_t(uint16_t(le)) << 48);
     for (const qsv_gate &g : c->gates) {
         mix(uint64_t(g.kind) | uint64_t(g.q0) << 8 | uint64_t(g.q1) << 16 | uint64_t(g.arg) << 24 | uint64_t(g.layer) << 32);
         h ^= h >> 29;
@@ -269,7 +276,7 @@ qsv_status compiled_default_shape(const qsv_circuit *c, int lb, int le, bool oop
     for (int k = 0; k < 4 && fewest > 1; ++k) {
         const int *t = kTiles[k];
         std::shared_ptr<Plan> plan;
-        const qsv_status st = get_plan(c, lb, le, TileShape{t[0], t[1], t[2], oop}, plan);
+        const qsv_status st = select_plan(c, lb, le, TileShape{t[0], t[1], t[2]}, oop, reads_state, plan);
         if (st != QSV_OK) return st;
         if (plan->passes.size() >= fewest) continue;
         fewest = plan->passes.size();
@@ -302,13 +309,19 @@ int jit_mode(const qsv_circuit *c, const qsv_fuse_opts *opts) {
 // Tile shape of a call: the options' one, else the default.  Options that name
 // some of the shape are completed from the largest-tile default in every call,
 // so that all entry points take and refuse the same ones.
+struct CallForm {
+    bool gate_order = false;   // see default_shape
+    bool reads_state = false;  // see get_fused_plan
+    bool second = true;        // the workspace holds a second state
+};
 qsv_status resolve_shape(const qsv_circuit *c, const qsv_fuse_opts *opts, TileShape &sh, int lb, int le,
-                         bool gate_order = false) {
+                         CallForm form) {
     const bool named = opts && (opts->reg_qubits || opts->thread_qubits || opts->low_qubits);
-    sh = default_shape(c->n, gate_order || named);
+    sh = default_shape(c->n, form.gate_order || named);
     const int jm = jit_mode(c, opts);
-    if (!gate_order && jm && !named) {
-        const qsv_status st = compiled_default_shape(c, lb, le, oop_mode(c, opts, jm) != 0, sh);
+    if (!form.gate_order && jm && !named) {
+        const qsv_status st =
+            compiled_default_shape(c, lb, le, oop_mode(c, opts, jm), form.reads_state, form.second, sh);
         if (st != QSV_OK) return st;
     }
     if (opts) {
@@ -367,7 +380,7 @@ qsv_status time_sweep_passes(const qsv_circuit *c, int lb, int le, const qsv_fus
                              void *amps, void *workspace, size_t ws_bytes, hipStream_t s,
                              uint64_t max_tiles, std::vector<float> &ms) {
     TileShape sh;
-    qsv_status st = resolve_shape(c, opts, sh, lb, le, true);
+    qsv_status st = resolve_shape(c, opts, sh, lb, le, {true});
     if (st != QSV_OK) return st;
     const int jm = jit_mode(c, opts);
     if (sh.R == 0 || !jm) return fail(QSV_EUNSUPPORTED, "pass timing needs compiled pass kernels");
@@ -531,14 +544,15 @@ qsv_status sv_apply_fused(void *amps, const qsv_circuit *c, uint64_t branch, int
     opts = effective_opts(c, opts, layer_begin, layer_end, &tuned);
     if (opts && opts->plain) return sv_apply_plain(amps, c, branch, layer_begin, layer_end, stream);
     TileShape sh;
-    if ((st = resolve_shape(c, opts, sh, layer_begin, layer_end)) != QSV_OK) return st;
+    const Workspace ws{static_cast<char *>(workspace), ws_bytes};
+    if ((st = resolve_shape(c, opts, sh, layer_begin, layer_end, {false, true, holds_second(c, ws)})) != QSV_OK)
+        return st;
     if (sh.R == 0) return sv_apply_plain(amps, c, branch, layer_begin, layer_end, stream);
     if ((st = check_device()) != QSV_OK) return st;
     std::shared_ptr<Plan> plan;
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (const int jm = jit_mode(c, opts)) {
         void *scratch = nullptr;
-        const Workspace ws{static_cast<char *>(workspace), ws_bytes};
         if ((st = get_fused_plan(c, layer_begin, layer_end, sh, oop_mode(c, opts, jm), true, ws, 0, plan,
                                  &scratch, nullptr)) != QSV_OK)
             return st;
@@ -574,9 +588,11 @@ qsv_status sv_apply_fused_from(const void *src, void *dst, const qsv_circuit *c,
     if ((st = check_device()) != QSV_OK) return st;
     hipStream_t s = static_cast<hipStream_t>(stream);
     TileShape sh;
+    const Workspace ws{static_cast<char *>(workspace), ws_bytes};
     bool fused = !(opts && opts->plain);
     if (fused) {
-        if ((st = resolve_shape(c, opts, sh, layer_begin, layer_end)) != QSV_OK) return st;
+        if ((st = resolve_shape(c, opts, sh, layer_begin, layer_end, {false, false, holds_second(c, ws)})) != QSV_OK)
+            return st;
         fused = sh.R != 0;
     }
     const int jm = fused ? jit_mode(c, opts) : 0;
@@ -585,7 +601,6 @@ qsv_status sv_apply_fused_from(const void *src, void *dst, const qsv_circuit *c,
         // any pass count ends in dst and src is never written
         std::shared_ptr<Plan> plan;
         void *scratch = nullptr;
-        const Workspace ws{static_cast<char *>(workspace), ws_bytes};
         if ((st = get_fused_plan(c, layer_begin, layer_end, sh, oop_mode(c, opts, jm), false, ws, 0, plan,
                                  &scratch, nullptr)) != QSV_OK)
             return st;
@@ -651,7 +666,7 @@ static qsv_status sampler_create(const qsv_circuit *c, int layer_begin, int laye
     const qsv_fuse_opts *eo = effective_opts(c, opts, layer_begin, layer_end, &tuned);
     bool fused = !(eo && eo->plain);
     if (fused) {
-        if ((st = resolve_shape(c, eo, S->sh, layer_begin, layer_end)) != QSV_OK) return st;
+        if ((st = resolve_shape(c, eo, S->sh, layer_begin, layer_end, {})) != QSV_OK) return st;
         fused = S->sh.R != 0;
     }
     S->jm = fused ? jit_mode(c, eo) : 0;
@@ -1083,7 +1098,7 @@ qsv_status sv_simulate(void *amps, const qsv_circuit *c, uint64_t branch, int in
     TileShape sh;
     bool fused = !(opts && opts->plain);
     if (fused) {
-        if ((st = resolve_shape(c, opts, sh, layer_begin, layer_end, true)) != QSV_OK) return st;
+        if ((st = resolve_shape(c, opts, sh, layer_begin, layer_end, {true})) != QSV_OK) return st;
         fused = sh.R != 0;
     }
     std::shared_ptr<Plan> plan;
@@ -1180,7 +1195,7 @@ qsv_status sv_simulate_dot(void *amps, const qsv_circuit *c, uint64_t branch, in
     TileShape sh;
     bool fused = !(opts && opts->plain);
     if (fused) {
-        if ((st = resolve_shape(c, opts, sh, layer_begin, layer_end, true)) != QSV_OK) return st;
+        if ((st = resolve_shape(c, opts, sh, layer_begin, layer_end, {true})) != QSV_OK) return st;
         fused = sh.R != 0;
     }
     const int jm = fused ? jit_mode(c, opts) : 0;
@@ -1271,7 +1286,7 @@ qsv_status sv_workspace_bytes(const qsv_circuit *c, int layer_begin, int layer_e
     if (fused) {
         // (no default tile of 2^24 amplitudes or more is below 2^11: its size is
         // the same for every tile, so none has to be planned here)
-        qsv_status st = resolve_shape(c, opts, sh, layer_begin, layer_end, true);
+        qsv_status st = resolve_shape(c, opts, sh, layer_begin, layer_end, {true});
         if (st != QSV_OK) return st;
     }
     const int jm = (fused && sh.R) ? jit_mode(c, opts) : 0;
@@ -1288,7 +1303,7 @@ qsv_status sv_plan_info(const qsv_circuit *c, int layer_begin, int layer_end,
     qsv_fuse_opts tuned;
     opts = effective_opts(c, opts, layer_begin, layer_end, &tuned);
     TileShape sh;
-    qsv_status st = resolve_shape(c, opts, sh, layer_begin, layer_end);
+    qsv_status st = resolve_shape(c, opts, sh, layer_begin, layer_end, {});
     if (st != QSV_OK) return st;
     if (sh.R == 0) return fail(QSV_EUNSUPPORTED, "sv_plan_info: state too small for a tile");
     std::shared_ptr<Plan> plan;
@@ -1324,7 +1339,7 @@ qsv_status sv_debug_emulate(void *amps_host, const qsv_circuit *c, uint64_t bran
     qsv_fuse_opts tuned;
     opts = effective_opts(c, opts, layer_begin, layer_end, &tuned);
     TileShape sh;
-    qsv_status st = resolve_shape(c, opts, sh, layer_begin, layer_end);
+    qsv_status st = resolve_shape(c, opts, sh, layer_begin, layer_end, {false, true, true});
     if (st != QSV_OK) return st;
     if (sh.R == 0) return fail(QSV_EUNSUPPORTED, "sv_debug_emulate: state too small for a tile");
     std::shared_ptr<Plan> plan;
@@ -1338,7 +1353,7 @@ qsv_status sv_debug_emulate(void *amps_host, const qsv_circuit *c, uint64_t bran
         // forms are checked
         TileShape so;
         std::shared_ptr<Plan> in_order;
-        if ((st = resolve_shape(c, opts, so, layer_begin, layer_end, true)) != QSV_OK) return st;
+        if ((st = resolve_shape(c, opts, so, layer_begin, layer_end, {true})) != QSV_OK) return st;
         if ((st = get_plan(c, layer_begin, layer_end, so, in_order)) != QSV_OK) return st;
         std::vector<float> ordered(amps, amps + (size_t(2) << c->n));
         double norm2 = 0.0, diff2 = 0.0;
@@ -1374,13 +1389,39 @@ qsv_status sv_debug_emulate(void *amps_host, const qsv_circuit *c, uint64_t bran
     return QSV_OK;
 }
 
+qsv_status sv_debug_fused_plan(const qsv_circuit *c, int layer_begin, int layer_end, const qsv_fuse_opts *opts,
+                               int in_place, size_t ws_bytes, int *tile, int *n_passes) {
+    if (!c || !tile || !n_passes) return fail(QSV_EINVAL, "sv_debug_fused_plan: null argument");
+    if (layer_begin < 0) return fail(QSV_EINVAL, "sv_debug_fused_plan: layer_begin < 0");
+    qsv_fuse_opts tuned;
+    opts = effective_opts(c, opts, layer_begin, layer_end, &tuned);
+    TileShape sh;
+    char there;  // stands for the workspace, which no plan touches
+    const Workspace ws{ws_bytes ? &there : nullptr, ws_bytes};
+    qsv_status st = resolve_shape(c, opts, sh, layer_begin, layer_end, {false, in_place != 0, holds_second(c, ws)});
+    if (st != QSV_OK) return st;
+    if (sh.R == 0) return fail(QSV_EUNSUPPORTED, "sv_debug_fused_plan: state too small for a tile");
+    std::shared_ptr<Plan> plan;
+    void *scratch = nullptr;
+    const int jm = jit_mode(c, opts);
+    st = jm ? get_fused_plan(c, layer_begin, layer_end, sh, oop_mode(c, opts, jm), in_place != 0, ws, 0, plan, &scratch,
+                             nullptr)
+            : get_plan(c, layer_begin, layer_end, sh, plan);
+    if (st != QSV_OK) return st;
+    tile[0] = sh.R;
+    tile[1] = sh.T;
+    tile[2] = sh.c;
+    *n_passes = int(plan->passes.size());
+    return QSV_OK;
+}
+
 qsv_status sv_debug_jit_compile(const qsv_circuit *c, int layer_begin, int layer_end,
                                 const qsv_fuse_opts *opts, size_t *code_bytes, double *seconds) {
     if (!c) return fail(QSV_EINVAL, "sv_debug_jit_compile: null circuit");
     qsv_fuse_opts tuned;
     opts = effective_opts(c, opts, layer_begin, layer_end, &tuned);
     TileShape sh;
-    qsv_status st = resolve_shape(c, opts, sh, layer_begin, layer_end);
+    qsv_status st = resolve_shape(c, opts, sh, layer_begin, layer_end, {});
     if (st != QSV_OK) return st;
     if (sh.R == 0) return fail(QSV_EUNSUPPORTED, "sv_debug_jit_compile: state too small for a tile");
     std::shared_ptr<Plan> plan;

@@ -212,8 +212,9 @@ qsv_batch **partition_batch(qsv_partition *p, void ***ws);
 // tune.cpp: the shape sv_tune picked for this circuit and layer range, if any
 bool tuned_opts(const qsv_circuit *c, int lb, int le, qsv_fuse_opts *out);
 // capi.cpp: the default tile of compiled passes for this circuit and layer
-// range (sh is left alone below 2^24 amplitudes)
-qsv_status compiled_default_shape(const qsv_circuit *c, int lb, int le, bool oop, TileShape &sh);
+// range, for the plan that the call runs (sh is left alone below 2^24 amplitudes)
+qsv_status compiled_default_shape(const qsv_circuit *c, int lb, int le, int oop, bool reads_state, bool second,
+                                  TileShape &sh);
 // capi.cpp: per-pass times of the compiled sweep from |+>^n (for the tuner)
 // max_tiles > 0: every pass runs only its first max_tiles tiles (timing
 // on a sample of a large state; the result is not the sweep's)

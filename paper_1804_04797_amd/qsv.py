@@ -29,6 +29,7 @@ EXPORTS = ["circuit_create", "circuit_destroy", "circuit_info", "circuit_gates",
            "circuit_split", "sv_init", "sv_apply_fused", "sv_apply_plain", "sv_amplitudes",
            "sv_norm_fp64", "sv_branch_combine", "sv_simulate", "sv_simulate_c128", "sv_batch_create", "sv_batch_run",
            "sv_batch_destroy", "sv_plan_info", "sv_debug_emulate", "sv_debug_jit_compile",
+           "sv_debug_fused_plan",
            "sv_tune", "sv_apply_dense", "sv_debug_emulate_dense", "qsv_release_device_buffers",
            "circuit_inverse", "sv_inner_product", "sv_branch_combine_full",
            "circuit_partition_plan", "circuit_partition_create", "circuit_partition_info",
@@ -106,6 +107,7 @@ def lib():
         "sv_debug_batch_schedule": (st, [vp, vp, sz, i32, i32, u64, i32, P(u64)]),
         "sv_plan_info": (st, [vp, i32, i32, vp, P(i32), vp, vp, sz, vp, sz]),
         "sv_debug_emulate": (st, [vp, vp, u64, i32, i32, vp]),
+        "sv_debug_fused_plan": (st, [vp, i32, i32, vp, i32, sz, vp, P(i32)]),
         "sv_debug_jit_compile": (st, [vp, i32, i32, vp, P(sz), P(ctypes.c_double)]),
         "qsv_release_device_buffers": (st, []),
         "circuit_inverse": (st, [vp, P(vp)]),
@@ -453,6 +455,16 @@ def sv_debug_emulate(amps_host: np.ndarray, c, branch=0, layer_begin=0, layer_en
     assert amps_host.dtype == np.complex64 and amps_host.flags.c_contiguous
     _check(lib().sv_debug_emulate(_ptr(amps_host), c, ctypes.c_uint64(branch), layer_begin,
                                   layer_end, _opts(opts)))
+
+
+def sv_debug_fused_plan(c, layer_begin=0, layer_end=-1, opts=None, in_place=True, ws_bytes=0):
+    """((reg, thread, low), passes) of the plan that sv_apply_fused (in_place)
+    or sv_apply_fused_from runs."""
+    tile = np.zeros(3, np.int32)
+    npass = ctypes.c_int()
+    _check(lib().sv_debug_fused_plan(c, layer_begin, layer_end, _opts(opts), 1 if in_place else 0, ws_bytes,
+                                     _ptr(tile), ctypes.byref(npass)))
+    return tuple(int(x) for x in tile), npass.value
 
 
 def sv_debug_jit_compile(c, layer_begin=0, layer_end=-1, opts=None):
