@@ -8,6 +8,8 @@
 #include <map>
 #include <mutex>
 #include <string>
+#include <system_error>
+#include <thread>
 
 #include "jit.h"
 #include "kernels.h"
@@ -219,17 +221,19 @@ qsv_status get_plan(const qsv_circuit *cc, int lb, int le, TileShape sh,
                     std::shared_ptr<Plan> &out) {
     qsv_circuit *c = const_cast<qsv_circuit *>(cc);
     PlanKey key{lb, le, sh.R, sh.T, sh.c, sh.oop};
-    std::lock_guard<std::mutex> g(c->mu);
-    auto it = c->plans.find(key);
-    if (it != c->plans.end()) {
-        out = it->second;
-        return QSV_OK;
+    {
+        std::lock_guard<std::mutex> g(c->mu);
+        auto it = c->plans.find(key);
+        if (it != c->plans.end()) {
+            out = it->second;
+            return QSV_OK;
+        }
     }
     auto p = std::make_shared<Plan>();
-    qsv_status st = build_plan(*c, lb, le, sh, *p);
+    qsv_status st = build_plan(*c, lb, le, sh, *p);  // unlocked: several plans of a circuit are built at once
     if (st != QSV_OK) return st;
-    c->plans[key] = p;
-    out = p;
+    std::lock_guard<std::mutex> g(c->mu);
+    out = c->plans.emplace(key, p).first->second;
     return QSV_OK;
 }
 
@@ -271,17 +275,28 @@ qsv_status compiled_default_shape(const qsv_circuit *c, int lb, int le, int oop,
             return QSV_OK;
         }
     }
-    size_t fewest = ~size_t(0);
-    int best = 0;
-    for (int k = 0; k < 4 && fewest > 1; ++k) {
+    // the candidates side by side: one plan does not keep the cores busy (26
+    // qubits, depth 24, out of place, new handle: 111 ms one after another with
+    // the planner's former walk, 17.7 now; 27 for (5, 8, 5) alone then)
+    constexpr int kCount = int(sizeof(kTiles) / sizeof(kTiles[0]));
+    std::shared_ptr<Plan> plan[kCount];
+    std::vector<std::thread> pool;
+    const auto plan_tile = [&](int k) {
         const int *t = kTiles[k];
-        std::shared_ptr<Plan> plan;
-        const qsv_status st = select_plan(c, lb, le, TileShape{t[0], t[1], t[2]}, oop, reads_state, plan);
-        if (st != QSV_OK) return st;
-        if (plan->passes.size() >= fewest) continue;
-        fewest = plan->passes.size();
-        best = k;
+        return select_plan(c, lb, le, TileShape{t[0], t[1], t[2]}, oop, reads_state, plan[k]);
+    };
+    try {
+        for (int k = 1; k < kCount; ++k) pool.emplace_back([&, k] { (void)plan_tile(k); });
+    } catch (const std::system_error &) {  // no more threads to be had: planned below
     }
+    qsv_status st = plan_tile(0);
+    for (std::thread &t : pool) t.join();
+    int best = 0;
+    for (int k = 1; k < kCount && st == QSV_OK; ++k) {
+        if (!plan[k]) st = plan_tile(k);  // not planned, or failed there: its message is wanted here
+        if (st == QSV_OK && plan[k]->passes.size() < plan[best]->passes.size()) best = k;
+    }
+    if (st != QSV_OK) return st;
     sh = TileShape{kTiles[best][0], kTiles[best][1], kTiles[best][2]};
     std::lock_guard<std::mutex> g(mu);
     if (chosen.size() >= kKept) chosen.clear();

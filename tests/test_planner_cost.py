@@ -1,0 +1,53 @@
+"""A circuit that was not seen before is planned in a few milliseconds, and the
+plans are those that were recorded: the gate-order calls round as their plan
+says, so a plan is part of their result."""
+import hashlib
+import time
+
+import pytest
+
+from paper_1804_04797_amd import qsv, workloads
+
+PLANS = [  # qubits, depth, seed, out_of_place, hash of three tiles' plans from three layers on
+    (12, 20, 1, 1, "f20b8c41ba41bd82"),
+    (12, 20, 1, -1, "f20b8c41ba41bd82"),
+    (16, 16, 2, 1, "f2a68ee84782b9cb"),
+    (16, 16, 2, -1, "9524da732e63e689"),
+    (20, 24, 3, 1, "1bc588ab5bae2eb2"),
+    (20, 24, 3, -1, "dac788402e18bebf"),
+    (24, 16, 4, 1, "202affa46eeca25f"),
+    (24, 16, 4, -1, "4b36d285d2eb2cbb"),
+    (26, 24, 5, 1, "1d41a1af2068a0a4"),
+    (26, 24, 5, -1, "60b89e6afecfab74"),
+    (28, 23, 6, 1, "581361bd51500705"),
+    (28, 23, 6, -1, "2e0e6ffd48bb8740"),
+    (30, 20, 7, 1, "c0a9a3c43ed52aaf"),
+    (30, 20, 7, -1, "2dbf21971231a142"),
+]
+
+
+@pytest.mark.parametrize("n,depth,seed,oop,want", PLANS)
+def test_recorded_plans(n, depth, seed, oop, want):
+    c = qsv.circuit_create(*workloads.lattice_for_qubits(n), depth, seed)
+    h = hashlib.sha256()
+    for r, t, low in ((5, 7, 4), (5, 8, 5), (4, 8, 4)):
+        if r + t > n:
+            continue
+        for lb in (0, 1, depth // 2):
+            p = qsv.sv_plan_info(c, lb, -1, dict(reg_qubits=r, thread_qubits=t, low_qubits=low, jit=1,
+                                                 out_of_place=oop))
+            h.update(p["pass_of_gate"].tobytes() + p["order_in_pass"].tobytes() + repr(p["resident"]).encode())
+    assert h.hexdigest()[:16] == want
+
+
+def test_default_tile_of_a_new_circuit():
+    """Four candidate tiles of 26 qubits at depth 24, out of place: 18 ms on eight
+    cores, 27 ms for one tile and 111 ms for the four of them before; the
+    bound leaves room for a slow machine."""
+    best = 1e9
+    for k in range(9):
+        c = qsv.circuit_create(*workloads.lattice_for_qubits(26), 24, 500 + k)
+        t = time.perf_counter()
+        qsv.sv_plan_info(c, 1, -1)
+        best = min(best, time.perf_counter() - t)
+    assert best < 0.06
