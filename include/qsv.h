@@ -482,8 +482,8 @@ qsv_status sv_branch_combine(const void *a_tab, const void *b_tab, size_t n_bran
  * eq. (1), eqs. (6)-(7)): out[x] = s(x) * sum_b A_b[x_A] B_b[x_B] for all
  * 2^(n_a + n_b) indices x, a complex GEMM on matrix cores.  flags = 0: the
  * complex64 inputs are widened to FP64 and every product and sum is FP64
- * (v_mfma_f64_16x16x4f64, three real products per complex one: an infinite
- * or NaN input gives NaN), the result rounded once to a complex64 out_state;
+ * (v_mfma_f64_16x16x4f64; every product is exact, so each component is off by
+ * the roundings of its own sum), the result rounded once to a complex64 out_state;
  * QSV_COMBINE_OUT_C128: out_state is complex128 (no rounding);
  * QSV_COMBINE_FP32: FP32 products and accumulation on FP32 matrix cores
  * (twice the rate, FP32 rounding in the sums).  a_states: complex64

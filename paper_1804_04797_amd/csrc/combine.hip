@@ -7,33 +7,31 @@
 // s(x) = (-1)^{sum over folded pairs x_a x_b}.  As matrices, Psi = Ahat Bhat^T
 // with Ahat[x_A][b] = A_b[x_A], a complex GEMM of shape 2^nA x 2^nB x nb.
 //
-// The default form sums the branch products in FP64: the FP32 inputs are
-// widened and multiplied on v_mfma_f64_16x16x4f64, so every product is exact
-// and every partial sum an FP64 sum, rounded once, to the complex64 state or
-// not at all for a complex128 one.  Three real products make a complex one,
-//   P = Ar Br, Q = Ai Bi, S = (Ar + Ai)(Br + Bi):  re = P - Q, im = S - P - Q
-// (the sums of two widened FP32 values are exact but for exponents 29 apart),
-// a quarter less matrix-core work than four.  The error of a complex64 state
-// is its one rounding either way (2.5e-8 for 2^15 x 2^15 x 1024); a sum of
-// 1024 branches in FP64 is 1.4e-15 off (relative, in the 2-norm) where four
-// products are 1.3e-15 off, as P, Q and S are sums of half as many terms.
-// Non-finite inputs give non-finite outputs, of whichever kind.  The FP32
-// form (v_mfma_f32_16x16x4f32, FP32 accumulation, selected explicitly) keeps
-// four products: there the cancellation in S - P - Q would show.
+// It runs as two real GEMMs over an interleaved index k = 2b + part:
+//   Mr = sum_k A1[k] B1[k],  A1 = (Ar, -Ai),  B1 = (Br, Bi)
+//   Mi = sum_k A2[k] B1[k],  A2 = (Ai,  Ar)
+// The default form widens the FP32 inputs and multiplies on
+// v_mfma_f64_16x16x4f64: every product is exact and every partial sum an FP64
+// sum, so a component is off by the roundings of its own sum alone; the result
+// is rounded once, to the complex64 state or not at all for a complex128 one.
+// (Three real products per complex one, re = P - Q, im = S - P - Q, take 104 ms
+// where these take 135.6; but then a component is as far off as the larger one
+// of its amplitude, and a sum of 1024 branches 1.06 times as far in the 2-norm.)
+// The FP32 form (v_mfma_f32_16x16x4f32, FP32 accumulation) runs at twice the
+// matrix-core rate and is selected explicitly.
 //
 // The matrix cores bound all of it (a complex64 state is written once, the
 // branch tables are read from the caches), so a workgroup owns a large tile:
-// 128 x 128 outputs, eight waves with a 64 x 32 part each in FP64: 104.0 ms
-// for 2^15 x 2^15 x 1024, 63.4 TFLOP/s on the matrix cores (four products:
-// 131.6 ms, 66.8 TFLOP/s).  A small matrix has few such tiles (2^8 x 2^8:
-// four); below a tile for every CU it is cut into 32 x 32 tiles of four waves
-// (2^8 x 2^8 x 500: 255 us, now 25).  Branch chunks are staged in LDS as real and imaginary planes whose rows are 16 banks apart (an
-// operand read covers two rows at a time); the next chunk's global loads are
-// issued before the current chunk's MFMA work so that they overlap it.  The
-// epilogue applies s(x) and scatters the tile to the state's natural index
-// order through per-tile tables of the rows' and columns' output bits.  A
-// launch covers one block of rows and columns (CombineArgs): the whole matrix
-// for a two-part split, one value of the selector qubits for a three-part
+// 128 x 128 outputs, eight waves with a 64 x 32 part each in FP64: 135.6 ms for
+// 2^15 x 2^15 x 1024, 64.9 TFLOP/s.  A small matrix has few such tiles (2^8 x
+// 2^8: four); below a tile for every CU it is cut into 32 x 32 tiles of four
+// waves (2^8 x 2^8 x 500: 265 us, now 29).  Branch chunks are staged in LDS as k-major planes whose rows are
+// 16 banks apart (an operand read covers four rows at a time); the next chunk's
+// global loads are issued before the current chunk's MFMA work so that they
+// overlap it.  The epilogue applies s(x) and scatters the tile to the state's
+// natural index order through per-tile tables of the rows' and columns' output
+// bits.  A launch covers one block of rows and columns (CombineArgs): the whole
+// matrix for a two-part split, one value of the selector qubits for a three-part
 // partition.
 #include <hip/hip_runtime.h>
 
@@ -59,22 +57,22 @@ k_combine_gemm(const float2 *__restrict__ A, const float2 *__restrict__ B, uint6
     using Real = typename std::conditional<F64, double, float>::type;
     using Acc = typename std::conditional<F64, v4d, v4f>::type;
     constexpr int NTH = 64 * WR * WC, TM = 16 * MB * WR, TN = 16 * NB * WC;
-    constexpr int NA = F64 ? 3 : 2;  // accumulators of a block: P, Q, S or re, im
-    __shared__ __attribute__((aligned(16))) float ar[kBr][TM + 16];
-    __shared__ float ai[kBr][TM + 16], br[kBr][TN + 16], bi[kBr][TN + 16];
+    constexpr int kK = 2 * kBr;  // interleaved K per chunk
+    __shared__ __attribute__((aligned(16))) float a1[kK][TM + 16];
+    __shared__ float a2[kK][TM + 16], b1[kK][TN + 16];
     __shared__ uint64_t rowx[TM], rowf[TM], colx[TN];
     const uint32_t t = threadIdx.x, lane = t & 63u, w = t >> 6;
     const uint64_t i0 = uint64_t(blockIdx.x) * TM, j0 = uint64_t(blockIdx.y) * TN;
     // this wave's part: rows rw + [0, 16 MB), columns cw + [0, 16 NB)
     const uint32_t rw = (w % WR) * 16 * MB, cw = (w / WR) * 16 * NB;
     const uint32_t lr = lane & 15u, lk = lane >> 4;
-    Acc acc[MB][NB][NA];
+    Acc acc[MB][NB][2];  // re, im
 #pragma unroll
     for (int m = 0; m < MB; ++m)
 #pragma unroll
         for (int c = 0; c < NB; ++c)
 #pragma unroll
-            for (int q = 0; q < NA; ++q) acc[m][c][q] = Acc{0, 0, 0, 0};
+            for (int q = 0; q < 2; ++q) acc[m][c][q] = Acc{0, 0, 0, 0};
     // staging: thread t always loads one in-tile row of every BS-th branch
     constexpr int BA = NTH / TM, BB = NTH / TN;  // branches staged at once
     constexpr int PA = kBr / BA, PB = kBr / BB;  // staged elements per thread
@@ -107,59 +105,37 @@ k_combine_gemm(const float2 *__restrict__ A, const float2 *__restrict__ B, uint6
         __syncthreads();  // previous chunk's fragments are read
 #pragma unroll
         for (int q = 0; q < PA; ++q) {
-            ar[ba + BA * q][ra] = na_[q].x;
-            ai[ba + BA * q][ra] = na_[q].y;
+            const uint32_t b = ba + BA * q;
+            a1[2 * b][ra] = na_[q].x;
+            a1[2 * b + 1][ra] = -na_[q].y;
+            a2[2 * b][ra] = na_[q].y;
+            a2[2 * b + 1][ra] = na_[q].x;
         }
 #pragma unroll
         for (int q = 0; q < PB; ++q) {
-            br[bb + BB * q][rb] = nb_[q].x;
-            bi[bb + BB * q][rb] = nb_[q].y;
+            const uint32_t b = bb + BB * q;
+            b1[2 * b][rb] = nb_[q].x;
+            b1[2 * b + 1][rb] = nb_[q].y;
         }
         __syncthreads();
         if (b0 + kBr < nbr) fetch(b0 + kBr);  // in flight during the MFMA work
 #pragma unroll
-        for (int ks = 0; ks < kBr; ks += 4) {
-            Real fr[MB], fi[MB], gr[NB], gi[NB];
+        for (int ks = 0; ks < kK; ks += 4) {
+            Real f1[MB], f2[MB], g[NB];
 #pragma unroll
             for (int m = 0; m < MB; ++m) {
-                fr[m] = Real(ar[ks + lk][rw + m * 16 + lr]);
-                fi[m] = Real(ai[ks + lk][rw + m * 16 + lr]);
+                f1[m] = Real(a1[ks + lk][rw + m * 16 + lr]);
+                f2[m] = Real(a2[ks + lk][rw + m * 16 + lr]);
             }
 #pragma unroll
-            for (int c = 0; c < NB; ++c) {
-                gr[c] = Real(br[ks + lk][cw + c * 16 + lr]);
-                gi[c] = Real(bi[ks + lk][cw + c * 16 + lr]);
-            }
-            if constexpr (F64) {
-                Real fs[MB], gs[NB];
+            for (int c = 0; c < NB; ++c) g[c] = Real(b1[ks + lk][cw + c * 16 + lr]);
 #pragma unroll
-                for (int m = 0; m < MB; ++m) fs[m] = fr[m] + fi[m];
+            for (int m = 0; m < MB; ++m)
 #pragma unroll
-                for (int c = 0; c < NB; ++c) gs[c] = gr[c] + gi[c];
-#pragma unroll
-                for (int m = 0; m < MB; ++m)
-#pragma unroll
-                    for (int c = 0; c < NB; ++c) {
-                        acc[m][c][0] = mfma(fr[m], gr[c], acc[m][c][0]);
-                        acc[m][c][1] = mfma(fi[m], gi[c], acc[m][c][1]);
-                        acc[m][c][NA - 1] = mfma(fs[m], gs[c], acc[m][c][NA - 1]);
-                    }
-            } else {
-#pragma unroll
-                for (int m = 0; m < MB; ++m)
-#pragma unroll
-                    for (int c = 0; c < NB; ++c) {
-                        acc[m][c][0] = mfma(fr[m], gr[c], acc[m][c][0]);
-                        acc[m][c][1] = mfma(fi[m], gr[c], acc[m][c][1]);
-                    }
-#pragma unroll
-                for (int m = 0; m < MB; ++m)
-#pragma unroll
-                    for (int c = 0; c < NB; ++c) {
-                        acc[m][c][0] = mfma(-fi[m], gi[c], acc[m][c][0]);
-                        acc[m][c][1] = mfma(fr[m], gi[c], acc[m][c][1]);
-                    }
-            }
+                for (int c = 0; c < NB; ++c) {
+                    acc[m][c][0] = mfma(f1[m], g[c], acc[m][c][0]);
+                    acc[m][c][1] = mfma(f2[m], g[c], acc[m][c][1]);
+                }
         }
     }
     // epilogue: block (m, c) element r of this lane is row 4*lk + r (FP32
@@ -197,14 +173,7 @@ k_combine_gemm(const float2 *__restrict__ A, const float2 *__restrict__ B, uint6
 #pragma unroll
             for (int c = 0; c < NB; ++c) {
                 const uint64_t j = P.col_base + j0 + cw + c * 16 + lr;
-                double vr, vi;
-                if constexpr (F64) {
-                    vr = acc[m][c][0][r] - acc[m][c][1][r];
-                    vi = acc[m][c][NA - 1][r] - acc[m][c][0][r] - acc[m][c][1][r];
-                } else {
-                    vr = double(acc[m][c][0][r]);
-                    vi = double(acc[m][c][1][r]);
-                }
+                double vr = double(acc[m][c][0][r]), vi = double(acc[m][c][1][r]);
                 if (__popcll(fm & j) & 1) { vr = -vr; vi = -vi; }
                 if (out_c128) static_cast<double2 *>(out)[xa | xb[c]] = make_double2(vr, vi);
                 else static_cast<float2 *>(out)[xa | xb[c]] = make_float2(float(vr), float(vi));
@@ -254,10 +223,10 @@ hipError_t launch_combine_gemm(const float2 *A, const float2 *B, uint64_t nbr, c
         std::memcpy(Q.fold_b, P.fold_a, sizeof(Q.fold_b));
     }
     // 128 x 128 tiles when there is one for every CU, else 32 x 32 (500
-    // branches: 2^10 x 2^10 67 us against 205 on large tiles; 300 branches:
-    // 2^12 x 2^12 502 us on large tiles against 604).  Chunks of 8 branches
-    // keep the large tile's three sums per output in registers (104.0 ms for
-    // 2^15 x 2^15 x 1024; 106.3 with 16, which spills).
+    // branches: 2^10 x 2^10 89 us against 269 on large tiles; 300 branches:
+    // 2^12 x 2^12 680 us on large tiles).  The order of the products is the same
+    // for every tile and chunk (FP64, 2^15 x 2^15 x 1024: chunks of 8 branches
+    // 135.6 ms, of 16 135.2, 2^11 x 2^11 x 37 31 and 36 us).
     const bool large = Q.na_blk + Q.nb_blk >= 14 + 8;
     if (!fp64)
         return large ? launch_gemm<false, 4, 4, 2, 2, 16, 2>(X, Y, nbr, Q, out, out_c128, s)
