@@ -138,8 +138,6 @@ bool big_state(const qsv_batch *b, int n) { return b->jit_mode >= 0 && n >= kBig
 // most scratch of a plan for states that entries share; larger ones stay in the
 // entries' own buffers, for one more launch where they are overwritten
 constexpr size_t kShareScratch = size_t(64) << 20;
-// states of 15 qubits from which on each is held by one tile: one for each CU
-constexpr size_t kWholeStates = 256;
 // entries of one launch of a compiled pass (grid rows)
 constexpr size_t kGridRows = 65536;
 // whether a plan of n qubits with count entries runs as compiled passes
@@ -365,13 +363,10 @@ qsv_status build_tables(qsv_batch *b, int lb) {
                 // compiled passes over many states fill the device anyway, and
                 // the larger tile has fewer exchanges (2 x 1024 branch states
                 // of 15 qubits, nothing shared: 315 us against 387 us on (4, 8,
-                // 4)); with the whole state in one tile there is one pass over
-                // memory, not two (with shared prefixes: 238 us on (5, 10, 5)
-                // and (6, 9, 5), which takes longer to compile; 398 on (5, 8, 5))
-                const bool whole =
-                    c->n == 15 && sharers[c].size() >= kWholeStates && sharers[c].size() < kGridRows;
-                const int low = b->low ? b->low : 5;
-                sh = whole ? TileShape{5, 10, low} : TileShape{5, 8, low};
+                // 4)).  A tile of 2^15 amplitudes, the whole state, is no faster
+                // with shared prefixes (2 x 1024: 266 us, 258 on (5, 8, 5); 350
+                // states: 85 and 63).
+                sh = TileShape{5, 8, b->low ? b->low : 5};
             }
             const bool shared = compiled(b, c->n, sharers[c].size()) && lb == 1 &&
                                 sharing_pays(sharers[c].size(), 1ull << (c->n - sh.R - sh.T));
