@@ -205,17 +205,29 @@ size_t distinct(const std::vector<uint64_t> &branches, uint64_t bits) {
 // Entries that differ in their branches only and start from the same state are
 // the same state up to the first gate that takes the bits they differ in: it is
 // computed once and read from there.  What bounds batched compiled passes is
-// their arithmetic, so the gain is the gates not applied again (2 x 1024 branch
-// states of 15 qubits, five of ten branch bits after half of the layers: 336 ->
-// 238 us).  Only where the entries' tiles are more than the CUs hold at once (two
-// each): below, a pass takes the time of one tile, and the extra launches would
-// only be added.
-bool sharing_pays(size_t count, uint64_t tiles) { return tiles * count > 512; }
+// their arithmetic, so the gain is the gates not applied again; the cost are the
+// launches added.  A plan that runs alone has to save a number of gates times
+// tiles for that; beside other chains of launches, which fill the device as well,
+// the batch needs tiles for three rounds of the workgroups that the CUs hold (two
+// each).  Means of five processes, depth 14, us without and with:
+//   alone         15 q x 66  16000 saved  36 / 32    18 q x 20  34000  42 / 47
+//                 16 q x 66  40000        43 / 38    18 q x 33  66000  57 / 54
+//                 15 q x 512 194000      100 / 78
+//   side by side  2 x 130 of 15 q, 1040 tiles  87 / 96     2 x 16 of 18 q, 1024   77 / 82
+//                 130 of 12 + 16 q, 1170       81 / 87     2 x 33 of 18 q, 2112  125 / 96
+//                 2 x 100 of 16 q, 1600        95 / 91     2 x 512 of 15 q, 4096 193 / 162
+// Not for states held by one tile: a pass over one of them is bound by the tile's
+// own chain of ops, short enough already (14 q x 4096 393 / 388, 12 q x 4096 367 /
+// 372, 2 x 1024 states of 12 q 221 / 228).
+bool sharing_pays(double saved, uint64_t batch_tiles, bool alone) {
+    return alone ? saved >= 40e3 : batch_tiles >= 3 * 512;
+}
 
 // Branch level at which the circuit is cut in two plans, so that the first one
 // runs for few states: the cut with the fewest gates over all states, if that
-// saves a quarter of them; 0: none.
-int shared_levels(const qsv_circuit &c, int lb, const std::vector<uint64_t> &branches) {
+// saves a quarter of them and pays; 0: none.
+int shared_levels(const qsv_circuit &c, int lb, const std::vector<uint64_t> &branches, uint64_t tiles,
+                  uint64_t batch_tiles, bool alone) {
     std::vector<int> lev;
     std::vector<uint64_t> bits;
     branch_levels(c, lev, bits);
@@ -237,7 +249,7 @@ int shared_levels(const qsv_circuit &c, int lb, const std::vector<uint64_t> &bra
             cut = int(l);
         }
     }
-    return cut;
+    return sharing_pays((count * total - best) * double(tiles), batch_tiles, alone) ? cut : 0;
 }
 
 // The launches of a compiled plan.  After pass p one state
@@ -334,6 +346,7 @@ qsv_status build_tables(qsv_batch *b, int lb) {
     std::map<const qsv_circuit *, uint32_t> idx;
     std::map<const qsv_circuit *, std::vector<uint64_t>> sharers;  // the branches of each circuit
     for (size_t i = 0; i < b->circs.size(); ++i) sharers[b->circs[i]].push_back(b->branches[i]);
+    std::vector<qsv_circuit *> circuits;  // of the plans
     std::vector<TileShape> plan_shape;
     for (size_t i = 0; i < b->circs.size(); ++i) {
         auto it = idx.find(b->circs[i]);
@@ -368,17 +381,29 @@ qsv_status build_tables(qsv_batch *b, int lb) {
                 // states: 85 and 63).
                 sh = TileShape{5, 8, b->low ? b->low : 5};
             }
-            const bool shared = compiled(b, c->n, sharers[c].size()) && lb == 1 &&
-                                sharing_pays(sharers[c].size(), 1ull << (c->n - sh.R - sh.T));
-            const int cut = shared ? shared_levels(*c, lb, sharers[c]) : 0;
-            std::shared_ptr<Plan> p;
-            const qsv_status st = batch_plan(c, lb, cut, sh, p);
-            if (st != QSV_OK) return st;
-            it = idx.emplace(b->circs[i], uint32_t(b->plans.size())).first;
-            b->plans.push_back(p);
+            it = idx.emplace(b->circs[i], uint32_t(circuits.size())).first;
+            circuits.push_back(c);
             plan_shape.push_back(sh);
         }
         b->entry_plan[i] = it->second;
+    }
+    uint64_t batch_tiles = 0;
+    for (size_t p = 0; p < circuits.size(); ++p)
+        batch_tiles += uint64_t(sharers[circuits[p]].size()) << (circuits[p]->n - plan_shape[p].R - plan_shape[p].T);
+    std::vector<int> plan_cut;
+    for (size_t p = 0; p < circuits.size(); ++p) {
+        qsv_circuit *c = circuits[p];
+        const TileShape &sh = plan_shape[p];
+        const std::vector<uint64_t> &branches = sharers[c];
+        const uint64_t tiles = 1ull << (c->n - sh.R - sh.T);
+        // from layer 1 on the run starts every entry from |+>^n
+        const bool may = lb == 1 && tiles > 1 && compiled(b, c->n, branches.size());
+        const int cut = may ? shared_levels(*c, lb, branches, tiles, batch_tiles, circuits.size() == 1) : 0;
+        std::shared_ptr<Plan> plan;
+        const qsv_status st = batch_plan(c, lb, cut, sh, plan);
+        if (st != QSV_OK) return st;
+        b->plans.push_back(plan);
+        plan_cut.push_back(cut);
     }
     b->group.assign(b->plans.size(), {});
     for (size_t i = 0; i < b->circs.size(); ++i) b->group[b->entry_plan[i]].push_back(uint32_t(i));
@@ -393,8 +418,7 @@ qsv_status build_tables(qsv_batch *b, int lb) {
         if (b->plan_jit[p]) {
             std::vector<uint64_t> branches;
             for (uint32_t i : b->group[p]) branches.push_back(b->branches[i]);
-            // from layer 1 on the run starts every entry from |+>^n
-            const bool share = lb == 1 && sharing_pays(branches.size(), 1ull << (plan.n - plan.R - plan.T));
+            const bool share = plan_cut[p] > 0;
             const size_t bytes = sizeof(float2) << plan.n;
             size_t scratch = 0;
             share_passes(plan, branches, share, kShareScratch / bytes, b->rows[p], b->steps[p], &scratch);

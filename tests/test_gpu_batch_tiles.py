@@ -33,3 +33,16 @@ def test_15_qubit_states_on_the_2_13_tile(count, tmp_path, monkeypatch):
     src, n, _ = _source((5, 6, 2, 12), count, 900 + count, tmp_path, monkeypatch)
     assert n == 15
     assert set(re.findall(r"__launch_bounds__\((\d+)", src)) == {"256"}
+
+
+@pytest.mark.parametrize("lattice,count,shared", [
+    ((4, 6, 2, 14), 1024, False), ((7, 4, 1, 14), 2048, False),      # one tile holds a state of 12 or 14 qubits
+    ((6, 6, 2, 14), 20, False), ((6, 6, 2, 14), 64, True),           # 18 qubits
+    ((5, 6, 2, 14), 30, False), ((5, 6, 2, 14), 300, True), ((4, 7, 2, 14), 255, True)])
+def test_prefixes_shared_where_it_pays(lattice, count, shared, tmp_path, monkeypatch):
+    """A plan cut for sharing has more passes than the circuit's own plan, or other ones."""
+    src, n, half = _source(lattice, count, 70 + count, tmp_path, monkeypatch)
+    tile = {12: (5, 7, 5), 14: (5, 9, 5)}.get(n, (5, 8, 5))
+    own = qsv.sv_plan_info(half, 1, -1, dict(reg_qubits=tile[0], thread_qubits=tile[1], low_qubits=tile[2]))
+    passes = len(re.findall(r"extern \"C\" __global__", src))
+    assert (passes > own["n_passes"]) == shared, (passes, own["n_passes"])
