@@ -518,7 +518,8 @@ qsv_status sv_branch_combine_full(const void *a_states, const void *b_states, si
  * side streams for the capture when it has two or more branches).  Entries
  * of one circuit that start from |+>^n share the part of it that runs before
  * the branch bits they differ in (compiled plans; up to 64 MiB of device
- * memory per plan for the shared states, held until the batch is destroyed).
+ * memory per plan and 128 MiB per batch for the shared states, held until the
+ * batch is destroyed).
  * There is no persistent form: QSV_BATCH_PERSISTENT=1 makes sv_batch_create
  * return QSV_EUNSUPPORTED.
  *

@@ -135,9 +135,10 @@ constexpr int kLdsState = 14;
 // entries that share a plan from which on its kernels are compiled
 constexpr size_t kSharedPlan = 8;
 bool big_state(const qsv_batch *b, int n) { return b->jit_mode >= 0 && n >= kBigState; }
-// most scratch of a plan for states that entries share; larger ones stay in the
-// entries' own buffers, for one more launch where they are overwritten
-constexpr size_t kShareScratch = size_t(64) << 20;
+// most scratch of a batch for states that entries share, and of one plan; more
+// of them stay in the entries' own buffers, for one more launch where they are
+// overwritten
+constexpr size_t kShareScratch = size_t(128) << 20, kPlanScratch = size_t(64) << 20;
 // entries of one launch of a compiled pass (grid rows)
 constexpr size_t kGridRows = 65536;
 // whether a plan of n qubits with count entries runs as compiled passes
@@ -412,6 +413,7 @@ qsv_status build_tables(qsv_batch *b, int lb) {
     b->d_scratch.assign(b->plans.size(), nullptr);
     b->rows.assign(b->plans.size(), {});
     b->steps.assign(b->plans.size(), {});
+    size_t left = kShareScratch;
     for (size_t p = 0; p < b->plans.size(); ++p) {
         const Plan &plan = *b->plans[p];
         b->plan_jit[p] = !plan.passes.empty() && compiled(b, plan.n, b->group[p].size());
@@ -421,7 +423,7 @@ qsv_status build_tables(qsv_batch *b, int lb) {
             const bool share = plan_cut[p] > 0;
             const size_t bytes = sizeof(float2) << plan.n;
             size_t scratch = 0;
-            share_passes(plan, branches, share, kShareScratch / bytes, b->rows[p], b->steps[p], &scratch);
+            share_passes(plan, branches, share, std::min(kPlanScratch, left) / bytes, b->rows[p], b->steps[p], &scratch);
             if (scratch && hipMalloc(reinterpret_cast<void **>(&b->d_scratch[p]), scratch * bytes) != hipSuccess) {
                 (void)hipGetLastError();  // then in the entries' own states
                 b->d_scratch[p] = nullptr;
@@ -429,6 +431,7 @@ qsv_status build_tables(qsv_batch *b, int lb) {
                 b->steps[p].clear();
                 share_passes(plan, branches, share, 0, b->rows[p], b->steps[p], &scratch);
             }
+            left -= scratch * bytes;
             hipError_t e = hipMalloc(reinterpret_cast<void **>(&b->d_group_ents[p]),
                                      b->rows[p].size() * sizeof(BatchEntry));
             if (e != hipSuccess) return fail(QSV_ENOMEM, "sv_batch: group entry table");
