@@ -159,8 +159,9 @@ bool lds_shape(int n, int *R, int *T) {
 
 // Schedule of one tile shape's entries (qubits n[i], pass count np[i],
 // entry id ids[i]): per round, a segment per entry that has the pass, block
-// offsets within the round, and the round's first work item.
-void make_schedule(const std::vector<int> &n, const std::vector<size_t> &np, const std::vector<uint32_t> &ids, int L,
+// offsets within the round, and the round's first work item.  A round is one
+// launch: QSV_ERANGE above the blocks of one.
+qsv_status make_schedule(const std::vector<int> &n, const std::vector<size_t> &np, const std::vector<uint32_t> &ids, int L,
                    std::vector<BatchRound> &rounds, std::vector<BatchSeg> &segs, std::vector<uint64_t> &round_blocks,
                    uint64_t &items) {
     size_t max_passes = 0;
@@ -179,9 +180,11 @@ void make_schedule(const std::vector<int> &n, const std::vector<size_t> &np, con
         }
         rd.nseg = uint32_t(segs.size()) - rd.seg_off;
         rounds.push_back(rd);
+        if (blocks > kMaxBlocks) return fail(QSV_ERANGE, "sv_batch: too many tiles in one round");
         round_blocks.push_back(blocks);
         items += blocks;
     }
+    return QSV_OK;
 }
 
 // Branch bits that a pass depends on.
@@ -487,13 +490,13 @@ qsv_status build_tables(qsv_batch *b, int lb) {
         }
         std::vector<BatchRound> rounds;
         uint64_t items = 0;
-        make_schedule(nq, np, bs.entries, bs.R + bs.T, rounds, shape_segs[k], bs.round_blocks, items);
+        const qsv_status st =
+            make_schedule(nq, np, bs.entries, bs.R + bs.T, rounds, shape_segs[k], bs.round_blocks, items);
+        if (st != QSV_OK) return st;
         for (const BatchRound &rd : rounds) {
             bs.round_seg_off.push_back(int(rd.seg_off));
             bs.round_nseg.push_back(int(rd.nseg));
         }
-        for (uint64_t blocks : bs.round_blocks)
-            if (blocks > (1ull << 31)) return fail(QSV_ERANGE, "sv_batch: too many tiles in one round");
     }
     hipError_t e;
     if (!progs.empty()) {
@@ -795,7 +798,8 @@ qsv_status sv_debug_batch_schedule(const int *n_qubits, const int *passes, size_
     std::vector<BatchSeg> segs;
     std::vector<uint64_t> blocks;
     uint64_t items = 0;
-    make_schedule(nq, np, ids, tile_qubits, rounds, segs, blocks, items);
+    const qsv_status st = make_schedule(nq, np, ids, tile_qubits, rounds, segs, blocks, items);
+    if (st != QSV_OK) return st;
     if (items_out) *items_out = items;
     std::vector<uint64_t> done(count, 0);
     std::vector<std::vector<uint64_t>> runs(count);  // per entry: times each (pass, tile) ran

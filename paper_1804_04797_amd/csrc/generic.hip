@@ -562,7 +562,7 @@ hipError_t launch_tile_batch_t(const BatchSeg *segs, int nseg, const BatchEntry 
     static const hipError_t attr = allow_lds(&k_tile_batch<R, T, HALF>, lds);
     if (attr != hipSuccess) return attr;
     if (blocks == 0) return hipSuccess;
-    if (blocks > (1ull << 31)) return hipErrorInvalidValue;
+    if (blocks > kMaxBlocks) return hipErrorInvalidValue;
     hipLaunchKernelGGL((k_tile_batch<R, T, HALF>), dim3(unsigned(blocks)), dim3(1 << T), lds, s, segs, nseg, ents,
                        progs, round, init_plus);
     return hipGetLastError();

@@ -20,6 +20,8 @@ bool compiled_shape_supported(int R, int T);
 // or tile k's sum of |amp|^2 goes to norm[k].
 hipError_t launch_tile(const float2 *src, float2 *amps, int n, int R, int T, const GenProg &p, uint64_t branch,
                        int init, uint64_t basis, double *norm, hipStream_t s);
+// blocks of one launch (x dimension of a grid)
+constexpr uint64_t kMaxBlocks = (1ull << 31) - 1;
 // One program round of a batch: `blocks` tiles of the entries in segs.
 // blocks == 0 only prepares the kernel (outside a capture).  alone: no compiled
 // passes run beside it.
