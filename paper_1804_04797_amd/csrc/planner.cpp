@@ -64,6 +64,11 @@ TileShape default_shape(int n, bool gate_order) {
 
 namespace {
 
+// Most factors of 2^{-1/2} that are not applied yet at any point of a pass: the
+// amplitudes of a state of length 1 stay below 2^120 then, those of one 2^7 times
+// as long within FP32 (a pass of more butterflies returned infinities: 11 qubits,
+// 700 gates).
+constexpr int kMaxCarry = 240;
 // Thread slots hold the lowest resident index bits at load and store.
 constexpr bool kLanesLow = true;
 // Exchanges prefer thread slots 4 and 5 (cross-lane swaps, see build_plan).
@@ -375,6 +380,7 @@ qsv_status build_plan_weighted(const qsv_circuit &c, int lb, int le, TileShape s
         ProgBuilder pb;
         const int budget = kMaxOps - 3 - 2;  // keep room for a final XCHG and SCALE
         int m_nd = 0, phase = 0;
+        const auto full = [&] { return (nd_cap > 0 && m_nd >= nd_cap) || carry_half + m_nd >= kMaxCarry; };
         std::vector<int> sched;
         size_t remaining = porder.size();
         while (remaining > 0) {
@@ -386,7 +392,7 @@ qsv_status build_plan_weighted(const qsv_circuit &c, int lb, int le, TileShape s
                     if (dn[i] || pd[i] != 0) continue;
                     const G &x = d.g[i];
                     if (x.nd && !(sl.where[x.q0] >= 0 && sl.where[x.q0] < R)) continue;
-                    if (x.nd && nd_cap > 0 && m_nd >= nd_cap) continue;
+                    if (x.nd && full()) continue;
                     if (int(pb.ops.size()) + 1 > budget) break;
                     // emit
                     switch (x.kind) {
@@ -414,7 +420,7 @@ qsv_status build_plan_weighted(const qsv_circuit &c, int lb, int le, TileShape s
                 if (int(pb.ops.size()) + 1 > budget) break;
             }
             if (remaining == 0 || int(pb.ops.size()) + 3 > budget) break;
-            if (nd_cap > 0 && m_nd >= nd_cap) break;  // the other gates wait for a later pass
+            if (full()) break;  // the other gates wait for a later pass
             // Stuck: bring the qubits of ready non-diagonal gates into registers.
             std::vector<int> want;
             std::vector<int> next_use(n, 1 << 30);
@@ -638,7 +644,8 @@ qsv_status build_plan_weighted(const qsv_circuit &c, int lb, int le, TileShape s
         // have modulus <= 1): powers of two scale FP32 values exactly, so
         // deferring them changes no rounding and saves each intermediate
         // pass a multiply of every amplitude.  Only when the deferred growth
-        // would pass 2^60 does an intermediate pass apply its even part.
+        // would pass 2^60 does an intermediate pass apply its even part, and a
+        // pass ends where its own would reach 2^(kMaxCarry / 2).
         carry_half += m_nd;
         const bool last_gates = (n_done == NG) && !final_scaled;
         double mag = 1.0;
