@@ -345,6 +345,7 @@ qsv_status batch_plan(qsv_circuit *c, int lb, int cut, const TileShape &sh, std:
 qsv_status build_tables(qsv_batch *b, int lb) {
     drop_graph(b);
     free_tables(b);
+    b->built_lb = -1;  // nothing is there until all of it is
     b->plans.clear();
     b->entry_plan.assign(b->circs.size(), 0);
     std::map<const qsv_circuit *, uint32_t> idx;

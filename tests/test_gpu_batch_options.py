@@ -31,3 +31,22 @@ def test_low_qubits(n, count, tmp_path, monkeypatch):
     gates = qsv.circuit_info(c)[2]
     # one rounding of 2^-24 per gate on an amplitude of size 2^{-n/2}, on each side
     assert np.max(np.abs(states[0] - states[1])) * 2.0 ** (n / 2) <= 2 * 2.0 ** -24 * gates
+
+
+def test_run_after_a_run_that_could_not_be_planned():
+    """Tables are built per start of the run: a start whose tuned tile does not fit
+    is refused, the other one still runs."""
+    n = 21
+    c = qsv.circuit_create(*workloads.lattice_for_qubits(n), 6, 3)
+    qsv.sv_tune_set(c, dict(reg_qubits=5, thread_qubits=8, low_qubits=30, jit=1), layer_begin=0)
+    a = torch.empty(1 << n, dtype=torch.complex64, device="cuda:0")
+    batch = qsv.sv_batch_create([c])
+    qsv.sv_batch_run(batch, [a], init_plus=True)
+    torch.cuda.synchronize()
+    want = a.clone()
+    with pytest.raises(qsv.QsvError):
+        qsv.sv_batch_run(batch, [a], init_plus=False)
+    a.zero_()
+    qsv.sv_batch_run(batch, [a], init_plus=True)
+    torch.cuda.synchronize()
+    assert torch.equal(a, want)
