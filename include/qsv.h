@@ -588,7 +588,8 @@ qsv_status sv_tune_set(const qsv_circuit *c, int layer_begin, int layer_end, con
 /*
  * Plan inspection (host only, no device needed).  For the plan that a call
  * which does not work in place uses when its workspace holds a second state
- * (sv_apply_fused_from): *n_passes, and for each gate of the layer range
+ * (sv_apply_fused_from; without options sv_simulate and sv_simulate_dot take
+ * another tile, 5 + 8 qubits from 13 qubits on): *n_passes, and for each gate of the layer range
  * the pass it runs in (pass_of_gate[i], -1 if outside the range) and its
  * position in that pass's program (order_in_pass[i]); resident_mask[p] is
  * the bit set of qubits resident in pass p (cap entries).  Arrays may be

@@ -17,8 +17,8 @@
 // compiled with uniform regions left unstructurized, for the same reason).
 // Before, every gate of the pass program was an op of its own: a 16-qubit
 // sweep of 95 gates took 77 us, now 26 (tile (4, 8, 4)); the 20-qubit depth-10
-// simulation 131, now 75, the 23-qubit depth-14 one 375, now 222 (both on
-// (5, 8, 5), in gate order).
+// simulation 131, now 70, the 23-qubit depth-14 one 375, now 152 (both on
+// (5, 8, 5), in gate order, with what run_tile and stage_halves say below).
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
