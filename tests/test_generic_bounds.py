@@ -19,7 +19,7 @@ def test_emulated_programs_at_the_stated_bound(n, count, shape, br):
     done = 0
     for branch in range(32 if br else 1):
         gates = _gates(c, branch)
-        ref = sim.run(start, n, gates)
+        ref = sim.run(start.copy(), n, gates)
         norm = np.linalg.norm(ref)
         if norm <= 0.01:  # this branch's projections leave nothing
             continue
