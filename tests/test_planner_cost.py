@@ -2,6 +2,7 @@
 plans are those that were recorded: the gate-order calls round as their plan
 says, so a plan is part of their result."""
 import hashlib
+import os
 import time
 
 import pytest
@@ -40,6 +41,7 @@ def test_recorded_plans(n, depth, seed, oop, want):
     assert h.hexdigest()[:16] == want
 
 
+@pytest.mark.skipif(len(os.sched_getaffinity(0)) < 8, reason="a time on eight cores")
 def test_default_tile_of_a_new_circuit():
     """Four candidate tiles of 26 qubits at depth 24, out of place: 18 ms on eight
     cores, 27 ms for one tile and 111 ms for the four of them before; the
